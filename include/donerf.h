@@ -52,7 +52,9 @@ typedef enum donerf_status {
 } donerf_status;
 
 typedef enum donerf_precision {
-    DONERF_FP32 = 0, /* fp32 weights, features and activations, fp32 MFMA    */
+    DONERF_FP32 = 0, /* fp32 weights, features and activations: each the exact
+                        sum of three bf16 values, products from six bf16 MFMA
+                        products with fp32 accumulation                      */
     DONERF_BF16 = 1, /* bf16 weights, features and hidden activations (RNE),
                         fp32 accumulation, fp32 scores, heads, compositing;
                         sine, cosine, exp and reciprocal of the encoding and

@@ -20,10 +20,11 @@ struct donerf_handle {
     int32_t wscale[16];  // per streamed layer: E8M0 scale of fp8 weights (127 - s), else 127
     int device;
     hipStream_t stream;
-    void* d_frags;       // device: depth stream then shading stream
+    void* d_frags;       // device: depth stream then shading stream (fp32: layout.h rows32_layer_frags)
     float* bias;         // device
     float* bins;         // device: centres[B], widths[B], bounds[B + 1]
     int n_d_chunks, n_s_chunks, bias_len;
+    size_t s_off;        // bytes of the depth stream, where the shading stream begins
     int n_cu;            // compute units: workgroups of one full round
     float* partial;      // device: split-tail parts, n_cu * 256 rays * 5 floats
     float* static_scratch;         // device address of the static scratch (kernels.hip)
@@ -243,7 +244,8 @@ void pack_layer(int prec, int net, int kind, int hidx, int n_bins, const float* 
     const int NP = t16 && kind == kSHead ? 1 : lg.rb * 32 / rows_per / RPP;
     const int E = elems(prec), EB = elem_bytes(prec), U = units(prec);
     const size_t start = dst.size();
-    dst.resize(start + (size_t)layer_chunks(net, kind, n_bins) * kChunkBytes, 0);
+    dst.resize(start + (net == kF32 ? (size_t)rows32_layer_frags(kind, n_bins) * kFragBytes
+                                    : (size_t)layer_chunks(net, kind, n_bins) * kChunkBytes), 0);
     uint8_t* out = dst.data() + start;
     size_t f = 0;
     for (int p = 0; p < NP; ++p)
@@ -266,6 +268,33 @@ void pack_layer(int prec, int net, int kind, int hidx, int n_bins, const float* 
                         } else {
                             std::memcpy(dstp, &v, 4);
                         }
+                    }
+                }
+            }
+}
+
+// Append one layer of an fp32 network: every weight as three bf16 values in
+// the fragment order of layout.h rows32_layer_frags.
+void pack_rows32(int kind, int n_bins, const float* W, std::vector<uint8_t>& dst) {
+    const LayerGeom lg = layer_geom(kind, n_bins);
+    const int groups = kind == kSHead ? 4 : 2, rows = 64 / groups;
+    const int KS = kind == kSHead ? 9 : lg.kpad / 16, RB = kind == kSHead ? 1 : lg.rb;
+    const size_t start = dst.size();
+    dst.resize(start + (size_t)rows32_layer_frags(kind, n_bins) * kFragBytes, 0);
+    uint8_t* out = dst.data() + start;
+    for (int rb = 0; rb < RB; ++rb)
+        for (int ks = 0; ks < KS; ++ks, out += 3 * kFragBytes)
+            for (int lane = 0; lane < 64; ++lane) {
+                const int row = rows * rb + lane % rows, g = lane / rows;
+                if (row >= lg.out_rows) continue;
+                for (int e = 0; e < 8; ++e) {
+                    const int col = rows32_in_col(kind, ks, g, e);
+                    if (col < 0) continue;
+                    float x = W[(size_t)row * lg.in_cols + col];
+                    for (int p = 0; p < 3; ++p) {
+                        const uint16_t h = to_bf16(x);
+                        std::memcpy(out + p * kFragBytes + lane * 16 + e * 2, &h, 2);
+                        x -= bf16_value(x);   // exact: x and its bf16 share their leading bits
                     }
                 }
             }
@@ -305,30 +334,60 @@ int validate_render(const donerf_t* h, const float* poses, int32_t P, int32_t H,
 
 int ncap_for(int N) { return N <= 4 ? 4 : N <= 8 ? 8 : 16; }
 
-// Split of the last, partial round of tiles: n_full tiles run whole, the
-// remaining rem tiles are each split `split` ways by samples.
+// How a launch's rays are cut: tiles of tile_rays, n_full of them whole, the
+// remaining rem each split `split` ways by samples.
 struct TailPlan {
-    uint32_t n_full, rem, split;
+    uint32_t tile_rays, n_full, rem, split;
 };
 
+// Measured time of one round of tiles (every CU busy) of a size, in
+// microseconds: depth network with selection and launch, and each sample of
+// the shading network.  The first entry of a precision is its main kernel's
+// tile, the others rows_kernel.h's; fits of renders of 992 to 40,000 rays at
+// N = 1, 4 and 16, B = 128.  A smaller tile costs more per ray but its round is
+// shorter, so it wins where the larger tiles leave CUs idle.
+struct TileCost {
+    int prec;
+    uint32_t rays;
+    float depth, sample;
+};
+const TileCost kTileCosts[] = {
+    {kF32, 32 * kF32CB, 80.0f, 60.0f}, {kF32, 32, 43.0f, 34.0f},
+    {kBF16, 256, 37.0f, 28.0f},
+    {kFP8, 256, 24.0f, 19.0f},
+};
+constexpr float kCombineCost = 4.0f;   // the combine launch of a split tail
+
 TailPlan plan_tail(const donerf_t* h, uint32_t total_rays, int32_t N) {
-    // Full rounds of one workgroup per CU run as they are.  The tiles of a
-    // last, partial round are split by samples over up to n_cu / r
-    // workgroups each (every part recomputes the depth network), and a
-    // combine pass composites the parts.
-    const uint32_t rpb = (uint32_t)rays_per_block(h->prec);
-    const uint32_t tiles = (total_rays + rpb - 1) / rpb;
+    // For a tile size: full rounds of one workgroup per CU run as they are.
+    // The tiles of a last, partial round are split by samples over up to
+    // n_cu / r workgroups each (every part recomputes the depth network), and a
+    // combine pass composites the parts.  The size with the smallest estimate
+    // is taken, the main kernel's on a tie.
     const uint32_t round = (uint32_t)h->n_cu;
-    const uint32_t full = tiles / round * round, rem = tiles - full;
-    uint32_t split = rem ? round / rem : 1;
-    if (split > (uint32_t)N) split = (uint32_t)N;
-    if (split < 1) split = 1;
-    return TailPlan{split > 1 ? full : tiles, split > 1 ? rem : 0, split};
+    TailPlan best{};
+    float best_t = 0.0f;
+    for (const TileCost& c : kTileCosts) {
+        if (c.prec != h->prec) continue;
+        const uint32_t tiles = total_rays / c.rays + (total_rays % c.rays != 0);
+        const uint32_t full = tiles / round * round, rem = tiles - full;
+        uint32_t split = rem ? round / rem : 1;
+        if (split > (uint32_t)N) split = (uint32_t)N;
+        if (split < 1) split = 1;
+        const uint32_t part = ((uint32_t)N + split - 1) / split;   // samples of a split part
+        const float t = (float)(full / round) * (c.depth + (float)N * c.sample) +
+                        (rem ? c.depth + (float)part * c.sample + (split > 1 ? kCombineCost : 0.0f) : 0.0f);
+        if (best.tile_rays == 0 || t < best_t) {
+            best = TailPlan{c.rays, split > 1 ? full : tiles, split > 1 ? rem : 0, split};
+            best_t = t;
+        }
+    }
+    return best;
 }
 
 // Floats of split-tail scratch a plan writes: 5 per ray and part.
-size_t tail_floats(const donerf_t* h, const TailPlan& t) {
-    return t.split > 1 ? (size_t)5 * t.rem * (size_t)rays_per_block(h->prec) * t.split : 0;
+size_t tail_floats(const TailPlan& t) {
+    return t.split > 1 ? (size_t)5 * t.rem * t.tile_rays * t.split : 0;
 }
 
 // partial: split-tail scratch of partial_cap floats (the handle's buffer, or
@@ -342,7 +401,7 @@ int render_impl(donerf_t* h, const float* poses, int32_t P, int32_t H, int32_t W
     // every launch's scratch need is known before the first one is enqueued
     for (int32_t p0 = 0; p0 < P; p0 += kMaxPosesPerLaunch) {
         const int np = P - p0 < kMaxPosesPerLaunch ? P - p0 : kMaxPosesPerLaunch;
-        const size_t need = tail_floats(h, plan_tail(h, (uint32_t)(np * hw), N));
+        const size_t need = tail_floats(plan_tail(h, (uint32_t)(np * hw), N));
         if (need > partial_cap)
             return fail(DONERF_E_UNSUPPORTED, "the split tail needs " + std::to_string(need) +
                                                   " floats of scratch, " + std::to_string(partial_cap) +
@@ -352,7 +411,7 @@ int render_impl(donerf_t* h, const float* poses, int32_t P, int32_t H, int32_t W
     RenderArgs a;
     std::memset(&a, 0, sizeof a);
     a.d_frags = static_cast<const uint4*>(h->d_frags);
-    a.s_frags = static_cast<const uint4*>(h->d_frags) + (size_t)h->n_d_chunks * (kChunkBytes / 16);
+    a.s_frags = static_cast<const uint4*>(h->d_frags) + h->s_off / 16;
     a.bias = h->bias;
     a.bins = h->bins;
     a.n_d_chunks = h->n_d_chunks;
@@ -391,6 +450,7 @@ int render_impl(donerf_t* h, const float* poses, int32_t P, int32_t H, int32_t W
         const TailPlan tp = plan_tail(h, a.total_rays, N);
         a.n_full = tp.n_full;
         a.split = (int32_t)tp.split;
+        a.tile_rays = (int32_t)tp.tile_rays;
         a.partial = partial;
         std::memcpy(a.wscale, h->wscale, sizeof a.wscale);
         hipError_t e = launch_render(h->prec, ncap_for(N), place,
@@ -398,7 +458,7 @@ int render_impl(donerf_t* h, const float* poses, int32_t P, int32_t H, int32_t W
                                      tp.rem, h->stream);
         if (e != hipSuccess) return hip_fail(e, "render launch");
         if (tp.split > 1) {
-            e = launch_combine(h->prec, a, h->stream);
+            e = launch_combine(a, h->stream);
             if (e != hipSuccess) return hip_fail(e, "combine launch");
         }
         if (out_scores && c.select == DONERF_SELECT_TOPN_SOFTMAX) {
@@ -447,7 +507,7 @@ int donerf_create(const donerf_cfg* cfg, const float* weights, size_t n_weights,
     std::vector<float> bias, head_bias;
     int n_d_chunks = 0, n_s_chunks = 0;
     int32_t wscale[16];
-    size_t off = 0;
+    size_t off = 0, s_off = 0;
     for (int l = 0; l < 16; ++l) {
         const int kind = (l == 0 && positions) ? kDFirstPos : kKinds[l];
         const LayerGeom lg = layer_geom(kind, B);
@@ -460,14 +520,17 @@ int donerf_create(const donerf_cfg* cfg, const float* weights, size_t n_weights,
             const std::vector<float> folded =
                 fold_positions_layer(weights + off, B, prec != kF32, centres, cfg->far_dist);
             pack_layer(fp, prec, kind, -1, B, folded.data(), 0, frags);
+        } else if (prec == kF32) {
+            pack_rows32(kind, B, weights + off, frags);
         } else {
             pack_layer(fp, prec, kind, kind == kHiddenL ? l % 8 - 1 : -1, B, weights + off, s, frags);
         }
         (l < 8 ? n_d_chunks : n_s_chunks) += layer_chunks(prec, kind, B);
-        if (l == 7 && wide_cdf(*cfg)) {
+        if (l == 7 && wide_cdf(*cfg) && prec != kF32) {
             pack_layer(fp, prec, kind, -1, B, weights + off, s, frags);
             n_d_chunks += layer_chunks(prec, kind, B);
         }
+        if (l == 7) s_off = frags.size();
         off += blob_w_count(l, B, cfg->depth_input);
         // the depth head's bias (B-dependent length) goes last
         std::vector<float>& dst = l == 7 ? head_bias : bias;
@@ -487,6 +550,7 @@ int donerf_create(const donerf_cfg* cfg, const float* weights, size_t n_weights,
     h->stream = nullptr;
     h->n_d_chunks = n_d_chunks;
     h->n_s_chunks = n_s_chunks;
+    h->s_off = s_off;
     h->bias_len = (int)bias.size();
     h->h_bounds = bounds;
     h->h_centres = centres;

@@ -36,6 +36,7 @@ struct RenderArgs {
     uint32_t n_full;
     int32_t split;
     float* partial;
+    int32_t tile_rays;      // rays of a tile
     float focal, half_w, half_h;
     float cx, cy, cz;
     float radius;
@@ -67,12 +68,15 @@ constexpr int kBf16CB = DONERF_BF16_CB;
 constexpr int kBf16NW = DONERF_BF16_NW;
 constexpr int kBf16Occ = DONERF_BF16_OCC;
 
-// Rays handled by one workgroup (prec: layout.h Precision of the network;
-// the fp8 kernel has the bf16 kernel's launch shape).
-inline int rays_per_block(int prec) { return prec != kF32 ? kBf16NW * 32 * kBf16CB : 4 * 32; }
+// Rays of a tile of the main render kernel (prec: layout.h Precision of the
+// network; the fp8 kernel has the bf16 kernel's launch shape), and column
+// blocks of the fp32 one.
+constexpr int kF32CB = 2;
+inline int rays_per_block(int prec) { return prec != kF32 ? kBf16NW * 32 * kBf16CB : 32 * kF32CB; }
 
 // Launches a.n_full whole tiles plus n_split_tiles tiles split a.split ways.
-// place: layout.h Placement; din: layout.h DepthInput.
+// place: layout.h Placement; din: layout.h DepthInput; a.tile_rays: the main
+// kernel's, or rows_kernel.h's smaller tiles'.
 hipError_t launch_render(int prec, int ncap, int place, int din, const RenderArgs& a, uint32_t n_split_tiles,
                          hipStream_t stream);
 // The variants of one precision and placement (render_*.hip).
@@ -85,9 +89,11 @@ hipError_t launch_render_fp8_cdf(int ncap, int din, const RenderArgs& a, dim3 gr
 hipError_t launch_render_bf16_cdf_wide(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
 hipError_t launch_render_fp32_cdf_wide(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
 hipError_t launch_render_fp8_cdf_wide(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
-// Composites the split parts of rays [n_full * rays_per_block, total_rays)
-// into out_rgb / out_depth.
-hipError_t launch_combine(int prec, const RenderArgs& a, hipStream_t stream);
+// Tiles of 32 rays (render_rows_fp32.hip).
+hipError_t launch_rows_fp32(int cdf, int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
+// Composites the split parts of rays [n_full * tile_rays, total_rays) into
+// out_rgb / out_depth.
+hipError_t launch_combine(const RenderArgs& a, hipStream_t stream);
 // Floats of the static device scratch behind donerf_render_static_scratch:
 // the split tail's parts (5 floats per ray and part) of up to 256 compute
 // units x 256 rays, 1.25 MiB per device.

@@ -81,6 +81,8 @@ __global__ void __launch_bounds__(256) topn_kernel(const float* scores, int32_t 
 hipError_t launch_render(int prec, int ncap, int place, int din, const RenderArgs& a, uint32_t n_split_tiles,
                          hipStream_t stream) {
     const dim3 grid(a.n_full + n_split_tiles * (uint32_t)a.split);
+    if (a.tile_rays != rays_per_block(prec))   // fp32 networks' small tiles
+        return launch_rows_fp32(place != kPlaceTopN, ncap, din, a, grid, stream);
     if (place == kPlaceCdfWide)
         return prec == kFP8    ? launch_render_fp8_cdf_wide(ncap, din, a, grid, stream)
                : prec == kBF16 ? launch_render_bf16_cdf_wide(ncap, din, a, grid, stream)
@@ -119,8 +121,8 @@ hipError_t static_scratch_address(int device, float** out) {
     return hipSuccess;
 }
 
-hipError_t launch_combine(int prec, const RenderArgs& a, hipStream_t stream) {
-    const uint32_t first = a.n_full * (uint32_t)rays_per_block(prec);
+hipError_t launch_combine(const RenderArgs& a, hipStream_t stream) {
+    const uint32_t first = a.n_full * (uint32_t)a.tile_rays;
     const uint32_t n = a.total_rays - first;
     hipLaunchKernelGGL(combine_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, a.partial, a.split, first,
                        a.total_rays, a.out_rgb, a.out_depth);

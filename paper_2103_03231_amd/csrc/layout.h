@@ -203,6 +203,28 @@ DN_HD constexpr int layer_chunks(int net, int kind, int n_bins) {
                : (layer_frags(net, kind, n_bins) + kChunkFrags - 1) / kChunkFrags;
 }
 
+// fp32 networks (rows_kernel.h) hold every weight as three bf16 values and run
+// 32x32x16 steps of three fragments, one per plane: per layer 32-row block,
+// K step of 16, plane, without padding.  Their units of eight K elements are
+// numbered 2 ks + g in the order of a bf16 network's 32x32 layout.  The shading
+// head is one 16-row tile of nine 16x16x32 steps, lane group G reading unit
+// 4 u + G; its last step reads the skip's units.  The folded positions layer
+// keeps its fp32 fragments.
+DN_HD constexpr int rows32_layer_frags(int kind, int n_bins) {
+    return kind == kSHead       ? 9 * 3
+           : kind == kDFirstPos ? layer_geom(kind, n_bins).rb * ksteps(kF32, kPKPad)
+                                : layer_geom(kind, n_bins).rb * (layer_geom(kind, n_bins).kpad / 16) * 3;
+}
+// Logical input column for K step ks, lane group g, element e of such a layer
+// (the shading head: step, lane group G).
+DN_HD constexpr int rows32_in_col(int kind, int ks, int g, int e) {
+    return kind == kDFirst   ? d_feature(g, 8 * ks + e)
+           : kind == kSFirst ? s_feature(g, 8 * ks + e)
+           : kind != kSHead  ? chained_row(kBF16, ks, g, e)
+           : ks < 8          ? chained_row(kBF16, (4 * ks + g) / 2, g % 2, e)
+           : skip_feature(g % 2, 8 * (g / 2) + e) < 0 ? -1 : kHidden + skip_feature(g % 2, 8 * (g / 2) + e);
+}
+
 // Bias table: every layer's bias padded to 32 * rb floats; the depth
 // network's seven ReLU layers, the shading network's eight layers, then the
 // depth head (the one length that depends on B).

@@ -956,16 +956,17 @@ static_assert(kCdfWaveFloats >= 8 * 64 * 4 && kCdfWaveFloats % 4 == 0, "a pass's
 template <int PR, int CB, int NW, int OCC, int NCAP, int PLACE, int DIN>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 render_kernel(const RenderArgs a) {
-    constexpr int FP = PR == kFP8 ? kBF16 : PR;   // first layers, heads, features
+    static_assert(PR != kF32, "fp32 networks run on rows_kernel.h");
+    constexpr int FP = kBF16;   // first layers, heads, features
     using P = Prec<FP>;
     constexpr int E = P::E;
     // first depth layer: K steps of the encoded input or of the folded
     // positions input (always fp32 steps, 8 K each)
     constexpr int KS_D0 = DIN == kDinEncoded ? kDKPad / (2 * E) : kPKPad / (2 * Prec<kF32>::E);
-    constexpr int KS_H = kHidden / (2 * E);       // heads: 16 | 32
-    constexpr int KS_HID = ksteps(PR, kHidden);   // hidden layers: 16 | 32 | 4
-    constexpr int KS_S0 = kSKPad / (2 * E);       // 4 | 8
-    constexpr int KS_SK = kSkipKPad / (2 * E);    // 2 | 4
+    constexpr int KS_H = kHidden / (2 * E);       // heads: 16
+    constexpr int KS_HID = ksteps(PR, kHidden);   // hidden layers: 16 | 4
+    constexpr int KS_S0 = kSKPad / (2 * E);       // 4
+    constexpr int KS_SK = kSkipKPad / (2 * E);    // 2
 
     __shared__ u32x4 ring0[kChunkVec];
     __shared__ u32x4 ring1[kChunkVec];
@@ -1023,8 +1024,8 @@ render_kernel(const RenderArgs a) {
         v[2] = (ou[2] - a.cz) / a.dmax;
         float f[kDSlots];
         if constexpr (DIN == kDinEncoded) {
-            fourier<5, FP == kF32>(v, g, f);
-            fourier<2, FP == kF32>(ray[cb].r, g, f + 30);
+            fourier<5, false>(v, g, f);
+            fourier<2, false>(ray[cb].r, g, f + 30);
             f[42] = g ? ray[cb].r[0] : v[0];
             f[43] = g ? ray[cb].r[1] : v[1];
             f[44] = g ? ray[cb].r[2] : v[2];
@@ -1047,7 +1048,7 @@ render_kernel(const RenderArgs a) {
             }
             din[0][cb] = Prec<kF32>::pack(q);
             din[1][cb] = Prec<kF32>::pack(q + 4);
-            fourier<2, FP == kF32>(ray[cb].r, g, f + 30);
+            fourier<2, false>(ray[cb].r, g, f + 30);
         }
         // the direction skip of the last shading layer: the same direction
         // encoding plus the identity
@@ -1212,7 +1213,7 @@ render_kernel(const RenderArgs a) {
                     st, g, BiasAt{bias_s, kDepthHeadBias + 32 * kRbPerPass * p}, g0,
                     [&](auto R, auto C, const f32x16& acc) {
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) vals[CV(C)][p][CV(R)][i] = sigmoid<FP == kF32>(acc[i]);
+                        for (int i = 0; i < 16; ++i) vals[CV(C)][p][CV(R)][i] = sigmoid<false>(acc[i]);
                         dump_scores(p, CV(R), CV(C), acc);
                     });
             } else {
@@ -1267,8 +1268,8 @@ render_kernel(const RenderArgs a) {
                 head_pass(PI, [&](auto R, auto C, const f32x16& acc) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const float v0 = sigmoid<FP == kF32>(acc[4 * q]), v1 = sigmoid<FP == kF32>(acc[4 * q + 1]);
-                        const float v2 = sigmoid<FP == kF32>(acc[4 * q + 2]), v3 = sigmoid<FP == kF32>(acc[4 * q + 3]);
+                        const float v0 = sigmoid<false>(acc[4 * q]), v1 = sigmoid<false>(acc[4 * q + 1]);
+                        const float v2 = sigmoid<false>(acc[4 * q + 2]), v3 = sigmoid<false>(acc[4 * q + 3]);
                         bs[(p * kRbPerPass + CV(R)) * 4 + q] = ((v0 + v1) + v2) + v3;
                     }
                     dump_scores(p, CV(R), CV(C), acc);
@@ -1336,10 +1337,10 @@ render_kernel(const RenderArgs a) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         f32x4 v;
-                        v[0] = sigmoid<FP == kF32>(acc[4 * q]);
-                        v[1] = sigmoid<FP == kF32>(acc[4 * q + 1]);
-                        v[2] = sigmoid<FP == kF32>(acc[4 * q + 2]);
-                        v[3] = sigmoid<FP == kF32>(acc[4 * q + 3]);
+                        v[0] = sigmoid<false>(acc[4 * q]);
+                        v[1] = sigmoid<false>(acc[4 * q + 1]);
+                        v[2] = sigmoid<false>(acc[4 * q + 2]);
+                        v[3] = sigmoid<false>(acc[4 * q + 3]);
                         *reinterpret_cast<f32x4*>(&cdf_s[tbase + 4 * ((CV(R) * 4 + q) * 64 + lane)]) = v;
                     }
                 });
@@ -1420,7 +1421,7 @@ render_kernel(const RenderArgs a) {
             for (int c = 0; c < 3; ++c) x[c] = ray[cb].o[c] + tk[cb] * ray[cb].r[c];
             warp(a, x, w);
             float f[kSSlots];
-            fourier<5, FP == kF32>(w, g, f);
+            fourier<5, false>(w, g, f);
             f[30] = g ? w[2] : w[0];
             f[31] = g ? 0.0f : w[1];
 #pragma unroll
@@ -1441,18 +1442,18 @@ render_kernel(const RenderArgs a) {
         // compositing of one sample from its head outputs (r, g, b, sigma)
         auto composite = [&](auto C, float hr, float hg, float hb, float hs) {
             constexpr int cb = CV(C);
-            const float cr = sigmoid<FP == kF32>(hr);
-            const float cg = sigmoid<FP == kF32>(hg);
-            const float cbl = sigmoid<FP == kF32>(hb);
+            const float cr = sigmoid<false>(hr);
+            const float cg = sigmoid<false>(hg);
+            const float cbl = sigmoid<false>(hb);
             const float sigma = fmaxf(hs, 0.0f);
             const float tau = sigma * dk[cb];
-            const float alpha = one_minus_exp_neg<FP == kF32>(tau);
+            const float alpha = one_minus_exp_neg<false>(tau);
             const float wgt = T[cb] * alpha;
             Cr[cb] += wgt * cr;
             Cg[cb] += wgt * cg;
             Cb[cb] += wgt * cbl;
             Dp[cb] += wgt * tk[cb];
-            T[cb] *= exp_neg<FP == kF32>(tau);
+            T[cb] *= exp_neg<false>(tau);
         };
         if constexpr (hid16(PR)) {
             head16<kChunkFrags * ((S0C + HIDC) & 1)>(st, lane >> 4, BiasAt{bias_s, s_bias + 7 * 256}, h0, skip,

@@ -1,0 +1,68 @@
+"""A ray's result does not depend on the tile size its launch is cut into.
+
+Calls of a few thousand rays run on tiles of 32 or 64 rays, larger ones on the
+precision's main tile.  One view of 61 x 83 rays (an odd width, a last tile
+that is not full) is rendered alone and in launches of 4 and 32 copies, which
+the planner cuts differently; the depth network and the placement (scores,
+classes, sample depths and widths) must be bit-identical, the colours and
+depths equal up to the order in which a split ray's parts are composited: at
+most N partial sums of values below 1 (depths: below 10), each off by half an
+ulp (6e-8, and 5e-7 for values in [8, 16))."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2103_03231_amd import binding as b
+from paper_2103_03231_amd import inputs
+
+pytestmark = pytest.mark.gpu
+PREC = {"fp32": b.FP32, "bf16": b.BF16, "fp8": b.FP8}
+
+
+@pytest.mark.parametrize("precision,select,din,B,N", [
+    ("fp32", "topn", "encoded", 128, 4),
+    ("fp32", "topn", "positions", 64, 9),
+    ("fp32", "cdf", "encoded", 128, 3),
+    ("fp32", "cdf", "positions", 192, 16),
+    ("bf16", "topn", "positions", 192, 1),
+    ("bf16", "cdf", "encoded", 64, 5),
+    ("bf16", "cdf", "positions", 256, 16),
+    ("fp8", "topn", "encoded", 64, 16),
+    ("fp8", "cdf", "positions", 128, 2),
+    ("fp8", "cdf", "encoded", 192, 6),
+])
+def test_tile_size_does_not_change_a_ray(precision, select, din, B, N):
+    cfg = b.Config(n_bins=B, n_max=N, precision=PREC[precision],
+                   select=b.SELECT_CDF if select == "cdf" else b.SELECT_TOPN,
+                   depth_input=b.DEPTH_POSITIONS if din == "positions" else b.DEPTH_ENCODED)
+    r = b.Renderer(cfg, inputs.make_weights(B, 3, din))
+    H, W = 83, 61
+    pose = inputs.make_poses([11])
+    alone = {k: v.cpu().numpy() for k, v in r.render(pose, H, W, N, depth=True, debug=True).items()}
+    assert np.isfinite(alone["rgb"]).all() and alone["rgb"].max() > 0
+    for copies in (4, 32):
+        out = r.render(np.repeat(pose, copies, axis=0), H, W, N, depth=True, debug=True)
+        torch.cuda.synchronize()
+        for i in range(copies):
+            for k in ("scores", "bins", "samples"):
+                assert np.array_equal(out[k][i].cpu().numpy(), alone[k][0]), (copies, i, k)
+            np.testing.assert_allclose(out["rgb"][i].cpu().numpy(), alone["rgb"][0], rtol=0, atol=N * 6e-8 + 1e-7)
+            np.testing.assert_allclose(out["depth"][i].cpu().numpy(), alone["depth"][0], rtol=0, atol=N * 5e-7 + 1e-6)
+    r.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16", "fp8"])
+def test_single_rays_match_a_frame(precision):
+    """Frames of 1, 31, 33, 63 and 65 rays (one row of the same view: the
+    tiles' edges) against themselves embedded in a batch of 32 views."""
+    r = b.Renderer(b.Config(precision=PREC[precision], n_max=4), inputs.make_weights(128, 3))
+    poses = inputs.make_poses(range(32))
+    for W in (1, 31, 33, 63, 65):
+        batch = r.render(poses, 1, W, 4, depth=True, debug=True)
+        for i in (0, 31):
+            one = r.render(poses[i:i + 1], 1, W, 4, depth=True, debug=True)
+            torch.cuda.synchronize()
+            for k in ("scores", "bins", "samples"):
+                assert torch.equal(one[k][0], batch[k][i]), (W, i, k)
+            assert float((one["rgb"][0] - batch["rgb"][i]).abs().max()) <= 4e-7
+    r.close()
