@@ -282,22 +282,26 @@ void pack_rows32(int kind, int n_bins, const float* W, std::vector<uint8_t>& dst
     const size_t start = dst.size();
     dst.resize(start + (size_t)rows32_layer_frags(kind, n_bins) * kFragBytes, 0);
     uint8_t* out = dst.data() + start;
-    for (int rb = 0; rb < RB; ++rb)
-        for (int ks = 0; ks < KS; ++ks, out += 3 * kFragBytes)
-            for (int lane = 0; lane < 64; ++lane) {
-                const int row = rows * rb + lane % rows, g = lane / rows;
-                if (row >= lg.out_rows) continue;
-                for (int e = 0; e < 8; ++e) {
-                    const int col = rows32_in_col(kind, ks, g, e);
-                    if (col < 0) continue;
-                    float x = W[(size_t)row * lg.in_cols + col];
-                    for (int p = 0; p < 3; ++p) {
-                        const uint16_t h = to_bf16(x);
-                        std::memcpy(out + p * kFragBytes + lane * 16 + e * 2, &h, 2);
-                        x -= bf16_value(x);   // exact: x and its bf16 share their leading bits
+    for (int ks = 0; ks < KS; ++ks)
+        for (int g = 0; g < groups; ++g) {
+            int col[8];
+            for (int e = 0; e < 8; ++e) col[e] = rows32_in_col(kind, ks, g, e);
+            for (int rb = 0; rb < RB; ++rb)
+                for (int r = 0; r < rows && rows * rb + r < lg.out_rows; ++r) {
+                    const float* w = W + (size_t)(rows * rb + r) * lg.in_cols;
+                    uint16_t h[3][8] = {};
+                    for (int e = 0; e < 8; ++e) {
+                        if (col[e] < 0) continue;
+                        float x = w[col[e]];
+                        for (int p = 0; p < 3; ++p) {
+                            h[p][e] = to_bf16(x);
+                            x -= bf16_value(x);   // exact: x and its bf16 share their leading bits
+                        }
                     }
+                    uint8_t* frag = out + (size_t)(rb * KS + ks) * 3 * kFragBytes + (g * rows + r) * 16;
+                    for (int p = 0; p < 3; ++p) std::memcpy(frag + p * kFragBytes, h[p], 16);
                 }
-            }
+        }
 }
 
 int check_device(int* dev_out) {
@@ -352,9 +356,9 @@ struct TileCost {
     float depth, sample;
 };
 const TileCost kTileCosts[] = {
-    {kF32, 32 * kF32CB, 80.0f, 60.0f}, {kF32, 32, 43.0f, 34.0f},
-    {kBF16, 256, 37.0f, 28.0f},
-    {kFP8, 256, 24.0f, 19.0f},
+    {kF32, 32 * kF32CB, 75.0f, 62.0f}, {kF32, 32, 43.0f, 34.5f},
+    {kBF16, 256, 40.0f, 31.0f},        {kBF16, 64, 18.5f, 12.2f}, {kBF16, 32, 15.0f, 7.8f},
+    {kFP8, 256, 28.0f, 20.5f},         {kFP8, 64, 15.5f, 7.6f},   {kFP8, 32, 12.0f, 5.5f},
 };
 constexpr float kCombineCost = 4.0f;   // the combine launch of a split tail
 

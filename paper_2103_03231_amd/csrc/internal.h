@@ -89,7 +89,9 @@ hipError_t launch_render_fp8_cdf(int ncap, int din, const RenderArgs& a, dim3 gr
 hipError_t launch_render_bf16_cdf_wide(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
 hipError_t launch_render_fp32_cdf_wide(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
 hipError_t launch_render_fp8_cdf_wide(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
-// Tiles of 32 rays (render_rows_fp32.hip).
+// rows_kernel.h's tiles: 32 rays, or 64 for bf16 and fp8 (render_rows_*.hip).
+hipError_t launch_rows_bf16(int cdf, int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
+hipError_t launch_rows_fp8(int cdf, int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
 hipError_t launch_rows_fp32(int cdf, int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
 // Composites the split parts of rays [n_full * tile_rays, total_rays) into
 // out_rgb / out_depth.

@@ -81,8 +81,12 @@ __global__ void __launch_bounds__(256) topn_kernel(const float* scores, int32_t 
 hipError_t launch_render(int prec, int ncap, int place, int din, const RenderArgs& a, uint32_t n_split_tiles,
                          hipStream_t stream) {
     const dim3 grid(a.n_full + n_split_tiles * (uint32_t)a.split);
-    if (a.tile_rays != rays_per_block(prec))   // fp32 networks' small tiles
-        return launch_rows_fp32(place != kPlaceTopN, ncap, din, a, grid, stream);
+    if (a.tile_rays != rays_per_block(prec)) {
+        const int cdf = place != kPlaceTopN;
+        return prec == kFP8    ? launch_rows_fp8(cdf, ncap, din, a, grid, stream)
+               : prec == kBF16 ? launch_rows_bf16(cdf, ncap, din, a, grid, stream)
+                               : launch_rows_fp32(cdf, ncap, din, a, grid, stream);
+    }
     if (place == kPlaceCdfWide)
         return prec == kFP8    ? launch_render_fp8_cdf_wide(ncap, din, a, grid, stream)
                : prec == kBF16 ? launch_render_bf16_cdf_wide(ncap, din, a, grid, stream)

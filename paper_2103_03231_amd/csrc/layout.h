@@ -215,14 +215,32 @@ DN_HD constexpr int rows32_layer_frags(int kind, int n_bins) {
            : kind == kDFirstPos ? layer_geom(kind, n_bins).rb * ksteps(kF32, kPKPad)
                                 : layer_geom(kind, n_bins).rb * (layer_geom(kind, n_bins).kpad / 16) * 3;
 }
+// The encodings of such a network go by pairs: elements 2 i and 2 i + 1 of unit
+// U hold the sine and cosine of argument q = 4 U + i, frequency q / 3 of
+// coordinate q % 3, so that one sincospi gives two features; the identities
+// follow.  pairs: arguments of the encoding; first: its first feature.
+DN_HD constexpr int pair_feature(int first, int q, int e) { return first + 3 + 6 * (q / 3) + q % 3 + 3 * (e % 2); }
+DN_HD constexpr int rows32_d_feature(int U, int e) {
+    return 4 * U + e / 2 < 30   ? pair_feature(0, 4 * U + e / 2, e)
+           : 4 * U + e / 2 < 42 ? pair_feature(63, 4 * U + e / 2 - 30, e)
+           : 8 * U + e < 87     ? 8 * U + e - 84
+           : 8 * U + e < 90     ? 63 + 8 * U + e - 87
+           : -1;
+}
+DN_HD constexpr int rows32_s_feature(int U, int e) {
+    return 4 * U + e / 2 < 30 ? pair_feature(0, 4 * U + e / 2, e) : 8 * U + e < 63 ? 8 * U + e - 60 : -1;
+}
+DN_HD constexpr int rows32_skip_feature(int U, int e) {
+    return 4 * U + e / 2 < 12 ? pair_feature(0, 4 * U + e / 2, e) : 8 * U + e < 27 ? 8 * U + e - 24 : -1;
+}
 // Logical input column for K step ks, lane group g, element e of such a layer
 // (the shading head: step, lane group G).
 DN_HD constexpr int rows32_in_col(int kind, int ks, int g, int e) {
-    return kind == kDFirst   ? d_feature(g, 8 * ks + e)
-           : kind == kSFirst ? s_feature(g, 8 * ks + e)
+    return kind == kDFirst   ? rows32_d_feature(2 * ks + g, e)
+           : kind == kSFirst ? rows32_s_feature(2 * ks + g, e)
            : kind != kSHead  ? chained_row(kBF16, ks, g, e)
            : ks < 8          ? chained_row(kBF16, (4 * ks + g) / 2, g % 2, e)
-           : skip_feature(g % 2, 8 * (g / 2) + e) < 0 ? -1 : kHidden + skip_feature(g % 2, 8 * (g / 2) + e);
+           : rows32_skip_feature(g, e) < 0 ? -1 : kHidden + rows32_skip_feature(g, e);
 }
 
 // Bias table: every layer's bias padded to 32 * rb floats; the depth

@@ -11,7 +11,16 @@
 // activations (the MFMA B operand) pass from layer to layer through LDS in
 // 16-byte units that the next layer reads as they are.  What bounds it is the
 // L2 read of a whole layer per R rays: small tiles trade that for using more
-// CUs.
+// CUs.  Measured per layer and workgroup, every CU busy: bf16 R = 32 2,400
+// cycles for 128 KiB (53 of the 64 bytes per cycle a CU takes from L2), R = 64
+// 3,250 (2,048 of them MFMAs); fp8 R = 32 1,550 for 64 KiB; fp32 R = 64 16,400
+// (12,288 of them MFMAs).
+//
+// bf16 and fp8 networks run the same MFMA steps on the same packed fragments in
+// the same K order as render_kernel.h, so scores, classes and samples are
+// bit-identical whichever of the two renders a ray.  Against that kernel's tiles
+// of 256 rays, 83 x 61 rays, N = 2, B = 64: 65.4 -> 30 us (tiles of 32); 128 x
+// 128, N = 4: 80 -> 66 us (tiles of 64).
 //
 // fp32 networks run on this kernel alone, on bf16 matrix cores: every fp32
 // value is the exact sum of three bf16 values, so a product is six bf16 MFMA
@@ -86,23 +95,19 @@ __device__ __forceinline__ void mma_split16(const u32x4* a, const u32x4* b, f32x
 
 // ------------------------------------------------------------------ encoding, one unit at a time
 
-// Slot s of the encoding of v (T frequency pairs 2t + g; fourier() above in
-// the same arithmetic): s / 6 the pair, s % 3 the coordinate, sine or cosine.
-template <bool EXACT>
-__device__ __forceinline__ float fourier_slot(float x, float y, float z, int g, int s) {
-    const int t = s / 6, c = s % 3;
-    const float v = c == 0 ? x : c == 1 ? y : z;
-    const float sc = (float)(1u << (2 * t)) * (g ? 2.0f : 1.0f);
-    float sn, co;
-    if constexpr (EXACT) {
-        sincospif(v * sc, &sn, &co);
-    } else {
-        const float yv = v * (0.5f * sc);
-        const float r = yv - __builtin_rintf(yv);
-        sn = __builtin_amdgcn_sinf(r);
-        co = __builtin_amdgcn_cosf(r);
-    }
-    return s % 6 < 3 ? sn : co;
+// Slot s of the encoding of v in fourier()'s order and arithmetic: s / 6 the
+// frequency pair, s % 3 the coordinate, sine or cosine.
+template <int S>
+__device__ __forceinline__ float fourier_slot(const float (&v)[3], int g) {
+    const float y = v[S % 3] * ((float)(1u << (2 * (S / 6))) * 0.5f * (g ? 2.0f : 1.0f));
+    const float r = y - __builtin_rintf(y);
+    return S % 6 < 3 ? __builtin_amdgcn_sinf(r) : __builtin_amdgcn_cosf(r);
+}
+
+// Argument q of an encoding by pairs (layout.h pair_feature).
+__device__ __forceinline__ void fourier_pair(const float (&v)[3], int q, float& sn, float& co) {
+    const int f = q / 3, c = q - 3 * f;
+    sincospif((c == 0 ? v[0] : c == 1 ? v[1] : v[2]) * (float)(1u << f), &sn, &co);
 }
 
 // ------------------------------------------------------------------ selection over the lanes of a ray
@@ -113,17 +118,26 @@ __device__ __forceinline__ float fourier_slot(float x, float y, float z, int g, 
 // max(a[k], b[NCAP - 1 - k]), a bitonic sequence that log2(NCAP) stages of
 // compare-exchange sort: NCAP + NCAP log2(NCAP) f64 operations per merge
 // where inserting one list into the other takes 2 NCAP^2.
+// The partners are DPP permutations within a row of 16 lanes: neighbours,
+// pairs, and the mirrors of 8 and 16 lanes (which pair the two halves, whose
+// lanes hold equal lists by then).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
 template <int NCAP, int LANES>
 __device__ __forceinline__ void merge_lanes(TopList<NCAP>& top) {
+    static_assert(LANES == 8 || LANES == 16, "lanes of a ray lie in one DPP row");
     using TL = TopList<NCAP>;
-#pragma unroll
-    for (int m = 1; m < LANES; m <<= 1) {
-        double o[NCAP];
-#pragma unroll
-        for (int k = 0; k < NCAP; ++k) o[k] = __shfl_xor(top.v[k], m);
+    sfor<(LANES == 16 ? 4 : 3)>([&](auto M) {
+        // quad_perm [1,0,3,2], quad_perm [2,3,0,1], row_half_mirror, row_mirror
+        constexpr int ctrl = CV(M) == 0 ? 0xB1 : CV(M) == 1 ? 0x4E : CV(M) == 2 ? 0x141 : 0x140;
         double w[NCAP];
 #pragma unroll
-        for (int k = 0; k < NCAP; ++k) w[k] = TL::kmax(top.v[k], o[NCAP - 1 - k]);
+        for (int k = 0; k < NCAP; ++k) w[k] = TL::kmax(top.v[k], dpp_f64<ctrl>(top.v[NCAP - 1 - k]));
 #pragma unroll
         for (int h = NCAP / 2; h >= 1; h >>= 1)
 #pragma unroll
@@ -135,7 +149,7 @@ __device__ __forceinline__ void merge_lanes(TopList<NCAP>& top) {
                 }
 #pragma unroll
         for (int k = 0; k < NCAP; ++k) top.v[k] = w[k];
-    }
+    });
 }
 
 // ------------------------------------------------------------------ the kernel body
@@ -187,12 +201,6 @@ struct RowsRender {
         return hid16(PR) ? 4 * (ks >> 1) + 2 * g + (ks & 1) : 2 * ks + g;
     }
     __device__ __forceinline__ u32x4* buf(int b) const { return sh.pool + (NBUF == 2 ? b * kActUnits : 0); }
-    // every wave has read what the next writes replace (two buffers: they
-    // replace what was read a barrier ago)
-    __device__ __forceinline__ void before_write() const {
-        if constexpr (NBUF == 1) lds_barrier();
-    }
-
     // ---- weights.  A wave reads the fragments of its own rows straight from
     // L2, kHeld of them ahead: they travel through one ring of registers that
     // runs on from layer to layer (fragment i of a stage in slot i % kHeld; each
@@ -218,7 +226,7 @@ struct RowsRender {
     }
     template <Map M, int SLOT0 = 0>
     __device__ __forceinline__ void preload(const u32x4* w) {
-        sfor<kHeld>([&](auto I) { ring[(CV(I) + SLOT0) % kHeld] = w[at(M, CV(I)) * 64]; });
+        sfor<kHeld>([&](auto I) { ring[(CV(I) + SLOT0) % kHeld] = w[at(M, CV(I)) * 64 + lane]; });
     }
     // Fragments I .. I + NF - 1 of a stage of F (mapping M, from w) are used:
     // request their successors (the next stage: mapping MN, from wn).
@@ -226,7 +234,7 @@ struct RowsRender {
     __device__ __forceinline__ void refill(const u32x4* w, const u32x4* wn) {
         sfor<NF>([&](auto J) {
             constexpr int i = I + CV(J), n = i + kHeld;
-            ring[(i + SLOT0) % kHeld] = n < F ? w[at(M, n) * 64] : wn[at(MN, n < F ? 0 : n - F) * 64];
+            ring[(i + SLOT0) % kHeld] = n < F ? w[at(M, n) * 64 + lane] : wn[at(MN, n < F ? 0 : n - F) * 64 + lane];
         });
     }
 
@@ -242,41 +250,38 @@ struct RowsRender {
     static constexpr int kBAhead = F32 ? 1 : CB == 1 ? 3 : 2;
 
     // KS steps of 16 K on 32x32x16 MFMAs for row block rows, into acc; unit(ks):
-    // the LDS unit of step ks for this lane.  RING: the fragments come from the
-    // ring (a stage of KS * PL), followed by the stage wn; otherwise from w.
-    // Column blocks cb0, cb0 + step, ... below CB.
-    template <int KS, Map MN, int SLOT0, class Unit>
-    __device__ __forceinline__ void steps32(const u32x4* w, const u32x4* wn, int cb0, int step, const u32x4* in,
-                                            Unit unit, f32x16 (&acc)[CB]) {
-        f32x16 lo[CB];
+    // the LDS unit of step ks for this lane; NC column blocks from cb0 on.  The
+    // fragments come from the ring (a stage of KS * PL), whose next stage is wn.
+    template <int KS, Map MN, int SLOT0, int NC, class Unit>
+    __device__ __forceinline__ void steps32(const u32x4* w, const u32x4* wn, int cb0, const u32x4* in, Unit unit,
+                                            f32x16 (&acc)[NC]) {
+        f32x16 lo[NC];
         if constexpr (F32) zero(lo);
-        u32x4 bv[kBAhead + 1][CB][PL];
+        u32x4 bv[kBAhead + 1][NC][PL];
         auto read_b = [&](auto K) {
             constexpr int ks = CV(K);
 #pragma unroll
-            for (int j = 0; j < CB; ++j)
-                if (cb0 + j * step < CB)
+            for (int j = 0; j < NC; ++j)
 #pragma unroll
-                    for (int p = 0; p < PL; ++p)
-                        bv[ks % (kBAhead + 1)][j][p] = in[(p * 32 + unit(ks)) * R + 32 * (cb0 + j * step) + col];
+                for (int p = 0; p < PL; ++p)
+                    bv[ks % (kBAhead + 1)][j][p] = in[(p * 32 + unit(ks)) * R + 32 * (cb0 + j) + col];
         };
         sfor<(kBAhead < KS ? kBAhead : KS)>(read_b);
         sfor<KS>([&](auto K) {
             constexpr int ks = CV(K);
             if constexpr (ks + kBAhead < KS) read_b(std::integral_constant<int, ks + kBAhead>{});
 #pragma unroll
-            for (int j = 0; j < CB; ++j)
-                if (cb0 + j * step < CB) {
-                    const u32x4* b = bv[ks % (kBAhead + 1)][j];
-                    if constexpr (F32) mma_split32(&ring[(3 * ks + SLOT0) % kHeld], b, acc[j], lo[j]);
-                    else acc[j] = Prec<kBF16>::mma(&ring[(ks + SLOT0) % kHeld], b, acc[j], 127);
-                }
+            for (int j = 0; j < NC; ++j) {
+                const u32x4* b = bv[ks % (kBAhead + 1)][j];
+                if constexpr (F32) mma_split32(&ring[(3 * ks + SLOT0) % kHeld], b, acc[j], lo[j]);
+                else acc[j] = Prec<kBF16>::mma(&ring[(ks + SLOT0) % kHeld], b, acc[j], 127);
+            }
             refill<KS * PL, kOneMap, MN, ks * PL, PL, SLOT0>(w, wn);
             __builtin_amdgcn_sched_barrier(0x6);
         });
         if constexpr (F32)
 #pragma unroll
-            for (int j = 0; j < CB; ++j) acc[j] = acc[j] + lo[j];
+            for (int j = 0; j < NC; ++j) acc[j] = acc[j] + lo[j];
     }
 
     // first layers: units in 32x32 order (2 ks + g)
@@ -287,8 +292,7 @@ struct RowsRender {
         const f32x16 b0 = bias_frag(bias + 32 * wave, g);
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) acc[cb] = b0;
-        steps32<KS, kHidMap, SLOT0>(w, wn, 0, 1, in, [&](int ks) { return 2 * ks + g; }, acc);
-        before_write();
+        steps32<KS, kHidMap, SLOT0>(w, wn, 0, in, [&](int ks) { return 2 * ks + g; }, acc);
         emit32<PR>(acc, out);
     }
 
@@ -305,50 +309,65 @@ struct RowsRender {
                 const u32x4 bv = in[(2 * ks + g) * R + 32 * cb + col];
                 acc[cb] = Prec<kF32>::mma(&av[ks], &bv, acc[cb], 127);
             }
-        before_write();
         emit32<PR>(acc, out);
     }
 
     // ReLU and rounding of this wave's 32-row block, written as the units of
-    // the next layer's input in precision OUT.
+    // the next layer's input in precision OUT.  With one buffer the rounding
+    // comes before the barrier, where the older wave of a SIMD, done first,
+    // runs it beside the younger one's MFMAs.
     template <int OUT>
     __device__ __forceinline__ void emit32(const f32x16 (&acc)[CB], u32x4* out) const {
+        constexpr int NU = OUT == kFP8 ? 1 : 2;
+        u32x4 o[CB][NU][PL];
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
-            const int c = 32 * cb + col;
             if constexpr (F32) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     float f[8];
 #pragma unroll
                     for (int i = 0; i < 8; ++i) f[i] = fmaxf(acc[cb][8 * h + i], 0.0f);
-                    u32x4 o[3];
-                    split3(f, o);
-#pragma unroll
-                    for (int p = 0; p < 3; ++p) out[(p * 32 + 2 * (2 * wave + h) + g) * R + c] = o[p];
+                    split3(f, o[cb][h]);
                 }
             } else if constexpr (OUT == kFP8) {
-                // elements 16 (wave % 2) .. + 15 of fp8 K step wave / 2
-                u32x4 o;
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
                     float v[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_fmed3f(acc[cb][4 * w + i], 0.0f, 448.0f);
+                    // the first convert's kept half is overwritten by the second
                     uint32_t x = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(v[0], v[1], __builtin_bit_cast(int, v[0]), false);
-                    o[w] = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(v[2], v[3], (int)x, true);
+                    o[cb][0][0][w] = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(v[2], v[3], (int)x, true);
                 }
-                out[(4 * (wave >> 1) + 2 * (wave & 1) + g) * R + c] = o;
             } else {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    u32x4 o;
+                for (int h = 0; h < 2; ++h)
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) o[w] = relu_bf16x2(acc[cb][8 * h + 2 * w], acc[cb][8 * h + 2 * w + 1]);
-                    out[unit32(2 * wave + h) * R + c] = o;
-                }
+                    for (int w = 0; w < 4; ++w)
+                        o[cb][h][0][w] = relu_bf16x2(acc[cb][8 * h + 2 * w], acc[cb][8 * h + 2 * w + 1]);
             }
         }
+        if constexpr (NBUF == 1) {
+            // held here: the compiler would sink the rounding past the barrier
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int h = 0; h < NU; ++h)
+#pragma unroll
+                    for (int p = 0; p < PL; ++p) asm volatile("" : "+v"(o[cb][h][p]));
+            lds_barrier();
+        }
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int h = 0; h < NU; ++h)
+#pragma unroll
+                for (int p = 0; p < PL; ++p) {
+                    // fp8: elements 16 (wave % 2) .. + 15 of K step wave / 2
+                    const int unit = OUT == kFP8 ? 4 * (wave >> 1) + 2 * (wave & 1) + g : unit32(2 * wave + h);
+                    out[(p * 32 + unit) * R + 32 * cb + col] = o[cb][h][p];
+                }
     }
 
     // a hidden layer; the next stage (mapping MN) follows at wn; OUT: precision
@@ -382,7 +401,7 @@ struct RowsRender {
                 refill<16, kHidMap, MN, 2 * ks, 2>(w, wn);
                 __builtin_amdgcn_sched_barrier(0x6);
             });
-            before_write();
+            static_assert(NBUF == 2, "bf16 activations fit twice");
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) {
                 const f32x4 &x = acc[0][ct], &y = acc[1][ct];
@@ -395,7 +414,7 @@ struct RowsRender {
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) acc[cb] = b0;
             if constexpr (F32) {
-                steps32<16, MN, 0>(w, wn, 0, 1, in, [&](int ks) { return 2 * ks + g; }, acc);
+                steps32<16, MN, 0>(w, wn, 0, in, [&](int ks) { return 2 * ks + g; }, acc);
             } else {
                 sfor<4>([&](auto K) {
                     constexpr int ks = CV(K);
@@ -407,13 +426,12 @@ struct RowsRender {
                     refill<8, kHidMap, MN, 2 * ks, 2>(w, wn);
                 });
             }
-            before_write();
             emit32<OUT>(acc, out);
         }
     }
     // six hidden layers from fragment stream w (the wave's first fragment of
     // layer 0), inputs and outputs alternating between the buffers, the first
-    // input in buffer 1
+    // input in buffer 1; the caller publishes the last output
     template <Map MN>
     __device__ __forceinline__ void hidden6(const u32x4* w, const u32x4* wn, int bias_off, const int32_t* ws) {
         constexpr size_t HF = (size_t)rows_layer_frags(PR, kHiddenL, 128) * 64;
@@ -423,7 +441,6 @@ struct RowsRender {
             lds_barrier();
         }
         hidden<MN, PR == kFP8 ? kBF16 : PR>(w + 5 * HF, wn, BiasAt{sh.bias, bias_off + 256 * 5}, buf(0), buf(1), ws[5]);
-        lds_barrier();
     }
 
     // ---- placement from the ray's scores in the pool; N samples per ray to
@@ -534,8 +551,8 @@ struct RowsRender {
         constexpr int KIND0 = DIN == kDinEncoded ? kDFirst : kDFirstPos;
         constexpr size_t D0F = rows_layer_frags(PR, KIND0, 128) * 64, HF = rows_layer_frags(PR, kHiddenL, 128) * 64,
                          S0F = rows_layer_frags(PR, kSFirst, 128) * 64;
-        const u32x4* dstream = reinterpret_cast<const u32x4*>(a.d_frags) + lane;
-        const u32x4* sstream = reinterpret_cast<const u32x4*>(a.s_frags) + lane;
+        const u32x4* dstream = reinterpret_cast<const u32x4*>(a.d_frags);
+        const u32x4* sstream = reinterpret_cast<const u32x4*>(a.s_frags);
         const int nrb = a.B / 32, groups = nrb <= 4 ? kRowWaves / nrb : 1;   // depth head: row blocks, waves on one
         const int rb = wave % nrb, cb0 = wave / nrb;
         const u32x4* d0 = dstream + one0(wave, KS_D0) * 64;
@@ -562,16 +579,16 @@ struct RowsRender {
         u32x4 pos_w[2];
         if constexpr (DIN == kDinEncoded) {
             sfor<(KS_D0 * PL < kHeld ? KS_D0 * PL : kHeld)>(
-                [&](auto I) { ring[(CV(I) + D0SLOT) % kHeld] = d0[at(kOneMap, CV(I)) * 64]; });
+                [&](auto I) { ring[(CV(I) + D0SLOT) % kHeld] = d0[at(kOneMap, CV(I)) * 64 + lane]; });
             // slots past the first layer's fragments: the first hidden layer's
             if constexpr (KS_D0 * PL < kHeld)
                 sfor<kHeld - KS_D0 * PL>([&](auto I) {
-                    ring[(KS_D0 * PL + CV(I) + D0SLOT) % kHeld] = dh[at(kHidMap, CV(I)) * 64];
+                    ring[(KS_D0 * PL + CV(I) + D0SLOT) % kHeld] = dh[at(kHidMap, CV(I)) * 64 + lane];
                 });
         } else {
             // two fp32 steps: pass of two row blocks, step, row block
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) pos_w[ks] = dstream[(((wave >> 1) * 2 + ks) * 2 + (wave & 1)) * 64];
+            for (int ks = 0; ks < 2; ++ks) pos_w[ks] = dstream[(((wave >> 1) * 2 + ks) * 2 + (wave & 1)) * 64 + lane];
             preload<kHidMap>(dh);
         }
         for (int k = tid; k < a.bias_len; k += kRowThreads) sh.bias[k] = a.bias[k];
@@ -608,31 +625,59 @@ struct RowsRender {
             const bool is_skip = task >= D_TASKS;
             const int tk = is_skip ? task - D_TASKS : task;
             const int ks = tk / CB, c = 32 * (tk % CB) + col;
-            const float r0 = sh.geo[3][c], r1 = sh.geo[4][c], r2 = sh.geo[5][c];
-            const float v0 = sh.geo[6][c], v1 = sh.geo[7][c], v2 = sh.geo[8][c];
+            const float r[3] = {sh.geo[3][c], sh.geo[4][c], sh.geo[5][c]};
+            const float v[3] = {sh.geo[6][c], sh.geo[7][c], sh.geo[8][c]};
             float f[8];
             if (is_skip) {
+                if constexpr (F32) {
+                    const int U = 2 * ks + g;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int s = 8 * ks + e;
-                    f[e] = s < 12 ? fourier_slot<F32>(r0, r1, r2, g, s)
-                         : s < 15 && !g ? (s == 12 ? r0 : s == 13 ? r1 : r2) : 0.0f;
+                    for (int i = 0; i < 4; ++i) {
+                        fourier_pair(r, min(4 * U + i, 11), f[2 * i], f[2 * i + 1]);
+                        if (U == 3) f[2 * i] = i == 0 ? r[0] : i == 1 ? r[2] : 0.0f, f[2 * i + 1] = i == 0 ? r[1] : 0.0f;
+                    }
+                } else {
+                    sfor<2>([&](auto K) {
+                        if (ks == CV(K))
+                            sfor<8>([&](auto E) {
+                                constexpr int s = 8 * CV(K) + CV(E);
+                                if constexpr (s < 12) f[CV(E)] = fourier_slot<s>(r, g);
+                                else f[CV(E)] = s < 15 && !g ? r[s % 12 % 3] : 0.0f;
+                            });
+                    });
                 }
-                // K step 8 of the 16x16 head reads unit G = 2 g + ks; the
-                // 32x32 head of an fp8 network unit 2 ks + g
-                store_unit(sh.skip, 4, PR == kFP8 ? 2 * ks + g : hid16(PR) ? 2 * g + ks : 2 * ks + g, c, f);
+                // K step 8 of the bf16 networks' 16x16 head reads unit
+                // G = 2 g + ks, the others 2 ks + g
+                store_unit(sh.skip, 4, hid16(PR) ? 2 * g + ks : 2 * ks + g, c, f);
             } else if constexpr (DIN == kDinEncoded) {
+                if constexpr (F32) {
+                    const int U = 2 * ks + g;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int s = 8 * ks + e;
-                    f[e] = s < 30 ? fourier_slot<F32>(v0, v1, v2, g, s)
-                         : s < 42 ? fourier_slot<F32>(r0, r1, r2, g, s - 30)
-                         : s == 42 ? (g ? r0 : v0) : s == 43 ? (g ? r1 : v1) : s == 44 ? (g ? r2 : v2) : 0.0f;
+                    for (int i = 0; i < 4; ++i) {
+                        const int q = 4 * U + i;
+                        const float x[3] = {q < 30 ? v[0] : r[0], q < 30 ? v[1] : r[1], q < 30 ? v[2] : r[2]};
+                        fourier_pair(x, q < 30 ? q : min(q - 30, 11), f[2 * i], f[2 * i + 1]);
+                        // the identities, 84 .. 89, then zeros
+                        if (q == 42) f[2 * i] = v[0], f[2 * i + 1] = v[1];
+                        else if (q == 43) f[2 * i] = v[2], f[2 * i + 1] = r[0];
+                        else if (q == 44) f[2 * i] = r[1], f[2 * i + 1] = r[2];
+                        else if (q > 44) f[2 * i] = f[2 * i + 1] = 0.0f;
+                    }
+                } else {
+                    sfor<KS_D0>([&](auto K) {
+                        if (ks == CV(K))
+                            sfor<8>([&](auto E) {
+                                constexpr int s = 8 * CV(K) + CV(E);
+                                if constexpr (s < 30) f[CV(E)] = fourier_slot<s>(v, g);
+                                else if constexpr (s < 42) f[CV(E)] = fourier_slot<s - 30>(r, g);
+                                else f[CV(E)] = s < 45 ? (g ? r[s % 3] : v[s % 3]) : 0.0f;
+                            });
+                    });
                 }
                 store_unit(buf(0), 32, 2 * ks + g, c, f);
             } else {
                 // [u', r, u_c] in fp32: unit (ks, g) holds K 8 ks + 2 e + g
-                const float q9[9] = {v0, v1, v2, r0, r1, r2, (sh.geo[0][c] - a.cx) / a.dmax,
+                const float q9[9] = {v[0], v[1], v[2], r[0], r[1], r[2], (sh.geo[0][c] - a.cx) / a.dmax,
                                      (sh.geo[1][c] - a.cy) / a.dmax, (sh.geo[2][c] - a.cz) / a.dmax};
                 float q[4];
 #pragma unroll
@@ -652,24 +697,26 @@ struct RowsRender {
         else first_layer_pos(pos_w, BiasAt{sh.bias, 0}, buf(0), buf(1));
         lds_barrier();
         hidden6<kOneMap>(dh, dhead, 256, a.wscale + 1);
+        lds_barrier();
         // ---- depth head: waves over row blocks, then over column blocks.  The
         // ring runs on into the shading network: fp32 its first layer, which
         // the others keep in registers of their own, then its hidden layers.
         {
-            const bool active = wave < nrb * groups && cb0 < CB;
-            f32x16 acc[CB];
-            const f32x16 b0 = bias_frag(BiasAt{sh.bias, kDepthHeadBias + 32 * rb}, g);
+            // B <= 128: one column block per wave (waves past the last compute
+            // the last one again and drop it); B > 128: all of them.
+            auto head = [&](auto NCc, int first, bool active) {
+                constexpr int NC = CV(NCc);
+                f32x16 acc[NC];
+                const f32x16 b0 = bias_frag(BiasAt{sh.bias, kDepthHeadBias + 32 * rb}, g);
 #pragma unroll
-            for (int j = 0; j < CB; ++j) acc[j] = b0;
-            steps32<KS_H, F32 ? kOneMap : kHidMap, 0>(dhead, F32 ? s0 : shd, active ? cb0 : CB, groups, buf(1),
-                                                      [&](int ks) { return unit32(ks); }, acc);
-            lds_barrier();   // the activations are read: the scores take their place
-            if (active) {
+                for (int j = 0; j < NC; ++j) acc[j] = b0;
+                steps32<KS_H, F32 ? kOneMap : kHidMap, 0>(dhead, F32 ? s0 : shd, first, buf(1),
+                                                          [&](int ks) { return unit32(ks); }, acc);
+                lds_barrier();   // the activations are read: the scores take their place
+                if (!active) return;
 #pragma unroll
-                for (int j = 0; j < CB; ++j) {
-                    const int cb = cb0 + j * groups;
-                    if (cb >= CB) continue;
-                    const int c = 32 * cb + col;
+                for (int j = 0; j < NC; ++j) {
+                    const int c = 32 * (first + j) + col;
                     if (a.out_scores && part == 0 && ray0 + c < a.total_rays) {
                         float* dst = a.out_scores + (size_t)(ray0 + c) * a.B + 32 * rb + 4 * g;
 #pragma unroll
@@ -689,7 +736,9 @@ struct RowsRender {
                         if constexpr (CDF) pre_row(c)[b + 1] = ((v[0] + v[1]) + v[2]) + v[3];
                     }
                 }
-            }
+            };
+            if (CB == 1 || nrb <= 4) head(std::integral_constant<int, 1>{}, min(cb0, CB - 1), cb0 < CB && wave < nrb * groups);
+            else head(std::integral_constant<int, CB>{}, 0, wave < nrb);
             lds_barrier();
             if constexpr (CDF) place_cdf();
             else select_topn();
@@ -708,13 +757,13 @@ struct RowsRender {
         u32x4 s0w[KS_S0];
         if constexpr (!F32)
 #pragma unroll
-            for (int ks = 0; ks < KS_S0; ++ks) s0w[ks] = s0[at(kOneMap, ks) * 64];
+            for (int ks = 0; ks < KS_S0; ++ks) s0w[ks] = s0[at(kOneMap, ks) * 64 + lane];
         for (int k = k_begin; k < k_end; ++k) {
             // Loads of weights that every sample reads again are loop-invariant,
             // and hoisted out they would be held in registers throughout:
             // pointers the compiler cannot see through keep them here.
             const u32x4 *s0k = s0, *shk = shd, *hk = shead;
-            asm volatile("" : "+v"(s0k), "+v"(shk), "+v"(hk));
+            asm volatile("" : "+s"(s0k), "+s"(shk), "+s"(hk));
             // the last head read buffer 1 (its only buffer, if there is one)
             if constexpr (NBUF == 1) lds_barrier();
             // tasks from the last wave down: the first waves run the head
@@ -726,11 +775,24 @@ struct RowsRender {
                 for (int i = 0; i < 3; ++i) x[i] = sh.geo[i][c] + t * sh.geo[3 + i][c];
                 warp(a, x, w);
                 float f[8];
+                if constexpr (F32) {
+                    const int U = 2 * ks + g;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int s = 8 * ks + e;
-                    f[e] = s < 30 ? fourier_slot<F32>(w[0], w[1], w[2], g, s)
-                         : s == 30 ? (g ? w[2] : w[0]) : (g ? 0.0f : w[1]);
+                    for (int i = 0; i < 4; ++i) {
+                        const int q = 4 * U + i;
+                        fourier_pair(w, min(q, 29), f[2 * i], f[2 * i + 1]);
+                        if (q == 30) f[2 * i] = w[0], f[2 * i + 1] = w[1];
+                        else if (q > 30) f[2 * i] = w[2], f[2 * i + 1] = 0.0f;
+                    }
+                } else {
+                    sfor<KS_S0>([&](auto K) {
+                        if (ks == CV(K))
+                            sfor<8>([&](auto E) {
+                                constexpr int s = 8 * CV(K) + CV(E);
+                                if constexpr (s < 30) f[CV(E)] = fourier_slot<s>(w, g);
+                                else f[CV(E)] = s == 30 ? (g ? w[2] : w[0]) : (g ? 0.0f : w[1]);
+                            });
+                    });
                 }
                 store_unit(buf(0), 32, 2 * ks + g, c, f);
             }
@@ -749,11 +811,19 @@ struct RowsRender {
                         const u32x4 bv = buf(0)[(2 * ks + g) * R + 32 * cb + col];
                         acc[cb] = Prec<kBF16>::mma(&s0w[ks], &bv, acc[cb], 127);
                     }
-                before_write();
                 emit32<PR>(acc, buf(1));
             }
             lds_barrier();
             hidden6<F32 ? kOneMap : kHidMap>(shk, F32 ? s0k : shk, s_bias + 256, a.wscale + 9);
+            // the head's first fragments are requested before the barrier
+            constexpr int HS = H16 ? 9 : KS_H + 2, HA = F32 ? 1 : HS;   // its K steps, and those held
+            u32x4 hw[HS][PL];
+            if (wave < HW)
+#pragma unroll
+                for (int u = 0; u < HA; ++u)
+#pragma unroll
+                    for (int p = 0; p < PL; ++p) hw[u][p] = hk[(PL * u + p) * 64 + lane];
+            lds_barrier();
             if (wave < HW) {
                 const u32x4* in = buf(1);
                 float h0, h1, h2, h3;
@@ -761,25 +831,23 @@ struct RowsRender {
                     f32x4 acc = *reinterpret_cast<const f32x4*>(sh.bias + s_bias + 7 * 256 + 4 * G), lo = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                     for (int u = 0; u < 9; ++u) {
-                        u32x4 av[PL], bv[PL];
+                        u32x4 bv[PL];
 #pragma unroll
                         for (int p = 0; p < PL; ++p) {
-                            av[p] = hk[(PL * u + p) * 64];
+                            if (u + HA < HS) hw[u + HA < HS ? u + HA : 0][p] = hk[(PL * (u + HA) + p) * 64 + lane];
                             bv[p] = u < 8 ? in[(p * 32 + 4 * u + G) * R + hc] : sh.skip[(p * 4 + G) * R + hc];
                         }
-                        if constexpr (F32) mma_split16(av, bv, acc, lo);
-                        else acc = mma16(av[0], bv[0], acc);
-                        if (F32 && u % 3 == 2) __builtin_amdgcn_sched_barrier(0x6);
+                        if constexpr (F32) mma_split16(hw[u], bv, acc, lo);
+                        else acc = mma16(hw[u][0], bv[0], acc);
                     }
                     if constexpr (F32) acc = acc + lo;
                     h0 = acc[0], h1 = acc[1], h2 = acc[2], h3 = acc[3];
                 } else {
                     f32x16 acc = bias_frag(BiasAt{sh.bias, s_bias + 7 * 256}, g);
 #pragma unroll
-                    for (int ks = 0; ks < KS_H + 2; ++ks) {
-                        const u32x4 av = hk[ks * 64];
+                    for (int ks = 0; ks < HS; ++ks) {
                         const u32x4 bv = ks < KS_H ? in[(2 * ks + g) * R + hc] : sh.skip[(2 * (ks - KS_H) + g) * R + hc];
-                        acc = Prec<kBF16>::mma(&av, &bv, acc, 127);
+                        acc = Prec<kBF16>::mma(hw[ks], &bv, acc, 127);
                     }
                     h0 = acc[0], h1 = acc[1], h2 = acc[2], h3 = acc[3];
                 }
