@@ -344,46 +344,51 @@ struct TailPlan {
     uint32_t tile_rays, n_full, rem, split;
 };
 
-// Measured time of one round of tiles (every CU busy) of a size, in
-// microseconds: depth network with selection and launch, and each sample of
-// the shading network.  The first entry of a precision is its main kernel's
-// tile, the others rows_kernel.h's; fits of renders of 992 to 40,000 rays at
-// N = 1, 4 and 16, B = 128.  A smaller tile costs more per ray but its round is
-// shorter, so it wins where the larger tiles leave CUs idle.
+// Measured time of one round of tiles of a size, per_cu of them on every CU, in
+// microseconds: depth network with selection and launch, and each sample of the
+// shading network; alone: the share of it that a round of at most one tile per
+// CU takes.  The first entry of a precision is its main kernel's tile, the
+// others rows_kernel.h's; fits of renders of 992 to 160,000 rays at N = 1, 4 and
+// 16, B = 128.  A smaller tile costs more per ray but its round is shorter, so it
+// wins where the larger tiles leave CUs idle.
 struct TileCost {
     int prec;
-    uint32_t rays;
-    float depth, sample;
+    uint32_t rays, per_cu;
+    float depth, sample, alone;
 };
 const TileCost kTileCosts[] = {
-    {kF32, 32 * kF32CB, 75.0f, 62.0f}, {kF32, 32, 43.0f, 34.5f},
-    {kBF16, 256, 40.0f, 31.0f},        {kBF16, 64, 18.5f, 12.2f}, {kBF16, 32, 15.0f, 7.8f},
-    {kFP8, 256, 28.0f, 20.5f},         {kFP8, 64, 15.5f, 7.6f},   {kFP8, 32, 12.0f, 5.5f},
+    {kF32, 32 * kF32CB, 1, 75.0f, 62.0f, 1.0f}, {kF32, 32, 1, 43.0f, 34.5f, 1.0f},
+    {kBF16, 256, 1, 40.0f, 31.0f, 1.0f},        {kBF16, 64, 1, 18.5f, 12.2f, 1.0f}, {kBF16, 32, 1, 15.0f, 7.8f, 1.0f},
+    {kFP8, 32 * kF8CB, 2, 32.0f, 21.5f, 0.66f}, {kFP8, 64, 1, 15.5f, 7.6f, 1.0f},   {kFP8, 32, 1, 12.0f, 5.5f, 1.0f},
 };
 constexpr float kCombineCost = 4.0f;   // the combine launch of a split tail
 
 TailPlan plan_tail(const donerf_t* h, uint32_t total_rays, int32_t N) {
-    // For a tile size: full rounds of one workgroup per CU run as they are.
-    // The tiles of a last, partial round are split by samples over up to
-    // n_cu / r workgroups each (every part recomputes the depth network), and a
-    // combine pass composites the parts.  The size with the smallest estimate
-    // is taken, the main kernel's on a tie.
-    const uint32_t round = (uint32_t)h->n_cu;
+    // For a tile size: full rounds of per_cu workgroups per CU run as they are.
+    // The r tiles of a last, partial round are split by samples, each over up to
+    // as many workgroups as one (or per_cu) per CU allows; every part recomputes
+    // the depth network, and a combine pass composites the parts.  The size and
+    // split with the smallest estimate are taken, the main kernel's on a tie.
     TailPlan best{};
     float best_t = 0.0f;
     for (const TileCost& c : kTileCosts) {
         if (c.prec != h->prec) continue;
+        const uint32_t round = (uint32_t)h->n_cu * c.per_cu;
         const uint32_t tiles = total_rays / c.rays + (total_rays % c.rays != 0);
         const uint32_t full = tiles / round * round, rem = tiles - full;
-        uint32_t split = rem ? round / rem : 1;
-        if (split > (uint32_t)N) split = (uint32_t)N;
-        if (split < 1) split = 1;
-        const uint32_t part = ((uint32_t)N + split - 1) / split;   // samples of a split part
-        const float t = (float)(full / round) * (c.depth + (float)N * c.sample) +
-                        (rem ? c.depth + (float)part * c.sample + (split > 1 ? kCombineCost : 0.0f) : 0.0f);
-        if (best.tile_rays == 0 || t < best_t) {
-            best = TailPlan{c.rays, split > 1 ? full : tiles, split > 1 ? rem : 0, split};
-            best_t = t;
+        const float t_full = (float)(full / round) * (c.depth + (float)N * c.sample);
+        for (uint32_t u = c.per_cu; u >= 1; --u) {
+            uint32_t split = rem ? (uint32_t)h->n_cu * u / rem : 1;
+            if (split > (uint32_t)N) split = (uint32_t)N;
+            if (split < 1) split = 1;
+            const uint32_t part = ((uint32_t)N + split - 1) / split;   // samples of a split part
+            const float load = rem * split <= (uint32_t)h->n_cu ? c.alone : 1.0f;
+            const float t = t_full + (rem ? load * (c.depth + (float)part * c.sample) + (split > 1 ? kCombineCost : 0.0f)
+                                          : 0.0f);
+            if (best.tile_rays == 0 || t < best_t) {
+                best = TailPlan{c.rays, split > 1 ? full : tiles, split > 1 ? rem : 0, split};
+                best_t = t;
+            }
         }
     }
     return best;

@@ -68,11 +68,14 @@ constexpr int kBf16CB = DONERF_BF16_CB;
 constexpr int kBf16NW = DONERF_BF16_NW;
 constexpr int kBf16Occ = DONERF_BF16_OCC;
 
-// Rays of a tile of the main render kernel (prec: layout.h Precision of the
-// network; the fp8 kernel has the bf16 kernel's launch shape), and column
-// blocks of the fp32 one.
+// 32-ray column blocks of the main kernels of fp32 and fp8 networks, and the
+// rays of a tile of each precision's main kernel (prec: layout.h Precision of
+// the network).
 constexpr int kF32CB = 2;
-inline int rays_per_block(int prec) { return prec != kF32 ? kBf16NW * 32 * kBf16CB : 32 * kF32CB; }
+constexpr int kF8CB = 4;
+inline int rays_per_block(int prec) {
+    return prec == kF32 ? 32 * kF32CB : prec == kFP8 ? 32 * kF8CB : kBf16NW * 32 * kBf16CB;
+}
 
 // Launches a.n_full whole tiles plus n_split_tiles tiles split a.split ways.
 // place: layout.h Placement; din: layout.h DepthInput; a.tile_rays: the main

@@ -65,7 +65,6 @@ template <>
 struct Prec<kBF16> {
     static constexpr int E = 8;      // K elements per lane per step
     static constexpr int U = 1;      // 1 KiB units (u32x4 per lane) per step, A and B alike
-    static constexpr int KSPB = 2;   // K steps produced per 32-row block
     __device__ static __forceinline__ f32x16 mma(const u32x4* a, const u32x4* b, f32x16 c, int) {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[0]),
                                                        __builtin_bit_cast(bf16x8, b[0]), c, 0, 0, 0);
@@ -80,7 +79,6 @@ template <>
 struct Prec<kF32> {
     static constexpr int E = 4;
     static constexpr int U = 1;
-    static constexpr int KSPB = 4;
     __device__ static __forceinline__ f32x16 mma(const u32x4* a, const u32x4* b, f32x16 c, int) {
         c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[0].x), __uint_as_float(b[0].x), c, 0, 0, 0);
         c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[0].y), __uint_as_float(b[0].y), c, 0, 0, 0);
@@ -128,28 +126,13 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 constexpr int kChunkVec = kChunkBytes / 16;  // u32x4 per chunk
-// LDS fragment reads in flight, in fragments: bf16 and fp32 fragments are
-// one 1 KiB unit, fp8 steps two.  Measured on 5 x 400 x 400, N = 4: 12 bf16
-// fragments ahead ran 2 % faster than 3 with 32x32 hidden layers; with the
-// 16x16 hidden layers 10 runs 0.4 % faster than 12 and 14 0.6 % slower; fp8
-// layers run best with 2 (of 2, 3, 4, 6).
+// LDS fragment reads in flight, in 1 KiB fragments.  Measured on 5 x 400 x
+// 400, N = 4: 12 ran 2 % faster than 3 with 32x32 hidden layers; with the 16x16
+// hidden layers 10 runs 0.4 % faster than 12 and 14 0.6 % slower.
 #ifndef DONERF_FRAG_AHEAD
 #define DONERF_FRAG_AHEAD 10
 #endif
-#ifndef DONERF_FRAG_AHEAD_FP8
-#define DONERF_FRAG_AHEAD_FP8 2
-#endif
 constexpr int kFragAhead = DONERF_FRAG_AHEAD;
-constexpr int kFragAheadFp8 = DONERF_FRAG_AHEAD_FP8;
-#ifndef DONERF_FP8_OVERLAP
-#define DONERF_FP8_OVERLAP 1
-#endif
-#ifndef DONERF_FP8_EPI_DELAY
-#define DONERF_FP8_EPI_DELAY 2
-#endif
-#ifndef DONERF_FP8_BIAS_LEAD
-#define DONERF_FP8_BIAS_LEAD 3
-#endif
 
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding).
 template <int VM>
@@ -299,161 +282,70 @@ __device__ __forceinline__ void run_pass(WS& st, int g, BiasAt bias, GetB& getB,
     sfor<RBP>([&](auto R) { sfor<CB>([&](auto C) { epi(R, C, acc[CV(R)][CV(C)]); }); });
 }
 
-// ReLU, round, and place a 32-row accumulator block as K steps
-// [ks0, ks0 + KSPB) of the next layer's B operand.  bf16: round to nearest
-// even, then ReLU on the packed pair as a signed 16-bit max with 0 (rounding
-// preserves the sign, so this equals rounding the ReLU).
-template <int PR, int NK, int CB>
-__device__ __forceinline__ void emit_relu(const f32x16& acc, u32x4 (&out)[NK][CB], int ks0, int cb) {
-    using P = Prec<PR>;
-    if constexpr (PR == kBF16) {
-        typedef short i16x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-        for (int h = 0; h < P::KSPB; ++h) {
-            u32x4 o;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const i16x2 v = __builtin_bit_cast(i16x2, pack_bf16x2(acc[8 * h + 2 * w], acc[8 * h + 2 * w + 1]));
-                o[w] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(v, i16x2{0, 0}));
-            }
-            out[ks0 + h][cb] = o;
-        }
-    } else {
-        float v[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = fmaxf(acc[i], 0.0f);
-#pragma unroll
-        for (int h = 0; h < P::KSPB; ++h) out[ks0 + h][cb] = P::pack(v + h * P::E);
-    }
-}
-
-// ReLU, clamp to the E4M3 range and round (nearest even) the two 32-row
-// blocks of a pass as K step ks of an fp8 layer's B operand: elements 0-15
-// are block 0's registers, 16-31 block 1's (layout.h chained_row).
+// ReLU, round, and place a 32-row accumulator block as K steps ks0 and
+// ks0 + 1 of the next layer's bf16 B operand: round to nearest even, then ReLU
+// on the packed pair as a signed 16-bit max with 0 (rounding preserves the
+// sign, so this equals rounding the ReLU).
 template <int NK, int CB>
-__device__ __forceinline__ void emit_fp8(const f32x16& a0, const f32x16& a1, u32x4 (&out)[NK][CB], int ks,
-                                         int cb) {
-    uint32_t d[8];
+__device__ __forceinline__ void emit_relu(const f32x16& acc, u32x4 (&out)[NK][CB], int ks0, int cb) {
+    typedef short i16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-    for (int w = 0; w < 8; ++w) {
-        const f32x16& v = w < 4 ? a0 : a1;
-        const int i = 4 * (w % 4);
-        const float v0 = __builtin_amdgcn_fmed3f(v[i + 0], 0.0f, 448.0f);
-        const float v1 = __builtin_amdgcn_fmed3f(v[i + 1], 0.0f, 448.0f);
-        const float v2 = __builtin_amdgcn_fmed3f(v[i + 2], 0.0f, 448.0f);
-        const float v3 = __builtin_amdgcn_fmed3f(v[i + 3], 0.0f, 448.0f);
-        // The convert writes one half of its tied operand and keeps the
-        // other; the second convert overwrites the half this one keeps, so
-        // the operand may be any register: v0's, which dies here, rather
-        // than a zero that costs a move per word.
-        uint32_t x = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(v0, v1, __builtin_bit_cast(int, v0), false);
-        x = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(v2, v3, (int)x, true);
-        d[w] = x;
+    for (int h = 0; h < 2; ++h) {
+        u32x4 o;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const i16x2 v = __builtin_bit_cast(i16x2, pack_bf16x2(acc[8 * h + 2 * w], acc[8 * h + 2 * w + 1]));
+            o[w] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(v, i16x2{0, 0}));
+        }
+        out[ks0 + h][cb] = o;
     }
-    out[2 * ks][cb] = u32x4{d[0], d[1], d[2], d[3]};
-    out[2 * ks + 1][cb] = u32x4{d[4], d[5], d[6], d[7]};
 }
 
-// Fully connected ReLU layer with 256 outputs (8 row blocks) as one software
-// pipeline over its KS * 8 fragments: passes of kRbPerPass row blocks use
-// alternating accumulator sets, so the bias/ReLU/rounding of pass p can
+// Fully connected ReLU layer with 256 bf16 outputs (8 row blocks) as one
+// software pipeline over its KS * 8 fragments: passes of kRbPerPass row blocks
+// use alternating accumulator sets, so the bias/ReLU/rounding of pass p can
 // overlap the MFMAs of pass p + 1, and LDS reads run kFragAhead fragments
-// ahead across pass and chunk boundaries.  OUT is the precision of the
-// output activations (the next layer's), MP that of the layer's own steps and
-// input; sa is the E8M0 scale of fp8 weights.  getB(k, c) returns the u32x4
-// k of the input (an fp8 step reads two).
-template <int OUT, int CB, int KS, int MP, int PAR0 = 0, bool PADDED = true, class WS, class GetB, int NOUT>
-__device__ __forceinline__ void hidden_layer(WS& st, int g, BiasAt bias, GetB&& getB,
-                                             u32x4 (&out)[NOUT][CB], int sa = 127) {
+// ahead across pass and chunk boundaries.  MP is the precision of the layer's
+// own steps and input.  getB(k, c) returns the u32x4 k of the input.
+template <int CB, int KS, int MP, int PAR0 = 0, bool PADDED = true, class WS, class GetB, int NOUT>
+__device__ __forceinline__ void first_layer(WS& st, int g, BiasAt bias, GetB&& getB, u32x4 (&out)[NOUT][CB]) {
     using M = Prec<MP>;
-    constexpr int U = M::U;
+    static_assert(M::U == 1, "first layers run single-unit steps");
     constexpr int RBP = kRbPerPass;
     constexpr int PF = KS * RBP;       // steps per pass
     constexpr int NF = 8 * KS;         // steps of the layer
-    constexpr int SPC = kChunkFrags / U;  // steps per chunk
-    constexpr int D = MP == kFP8 ? kFragAheadFp8 : kFragAhead;
-    static_assert(OUT != kFP8 || RBP == 2, "an fp8 K step takes two row blocks");
+    constexpr int SPC = kChunkFrags;   // steps per chunk
+    constexpr int D = kFragAhead;
     f32x16 acc[2][RBP][CB];
-    u32x4 a[D + 1][U];
-    constexpr int NP = 8 / RBP;        // passes
-    // Overlapped passes (fp8 steps): the next pass's biases are read into its
-    // accumulator set LEAD steps before the current pass ends, and a pass's
-    // epilogue runs DEL steps into the next pass.
-    constexpr bool OV = DONERF_FP8_OVERLAP && MP == kFP8;
-    constexpr int DEL = DONERF_FP8_EPI_DELAY < PF - 2 ? DONERF_FP8_EPI_DELAY : PF - 2;
-    constexpr int LEAD = DONERF_FP8_BIAS_LEAD < PF - DEL - 1 ? DONERF_FP8_BIAS_LEAD : PF - DEL - 1;
-    static_assert(!OV || LEAD >= 1, "overlap needs room between the epilogue and the next biases");
-    auto load_bias = [&](auto PP) {
-        constexpr int q = CV(PP);
-        sfor<RBP>([&](auto R) {
-            const f32x16 b = bias_frag(bias + 32 * (RBP * q + CV(R)), g);
-            sfor<CB>([&](auto C) { acc[q & 1][CV(R)][CV(C)] = b; });
-        });
-    };
-    auto epilogue = [&](auto PP) {
-        constexpr int p = CV(PP);
-        if constexpr (OUT == kFP8) {
-            sfor<CB>([&](auto C) { emit_fp8(acc[p & 1][0][CV(C)], acc[p & 1][1][CV(C)], out, p, CV(C)); });
-            // Pin the pass's outputs here: layers outside a loop could
-            // otherwise have their pure MFMA chains sunk past the later chunk
-            // barriers to the blocks that use them, holding every fragment of
-            // those chunks in registers.
-            sfor<CB>([&](auto C) {
-                const u32x4 o0 = out[2 * p][CV(C)], o1 = out[2 * p + 1][CV(C)];
-                asm volatile("" ::"v"(o0), "v"(o1));
-            });
-        } else if constexpr (MP == kFP8) {
-            sfor<RBP>([&](auto R) {
-                sfor<CB>([&](auto C) {
-                    emit_relu<OUT>(acc[p & 1][CV(R)][CV(C)], out, (p * RBP + CV(R)) * Prec<OUT>::KSPB, CV(C));
-                    sfor<Prec<OUT>::KSPB>([&](auto H) {
-                        const u32x4 o = out[(p * RBP + CV(R)) * Prec<OUT>::KSPB + CV(H)][CV(C)];
-                        asm volatile("" ::"v"(o));
-                    });
-                });
-            });
-        } else {
-            sfor<RBP>([&](auto R) {
-                sfor<CB>([&](auto C) {
-                    emit_relu<OUT>(acc[p & 1][CV(R)][CV(C)], out, (p * RBP + CV(R)) * Prec<OUT>::KSPB, CV(C));
-                });
-            });
-        }
-    };
+    u32x4 a[D + 1];
     sfor<NF + D>([&](auto S) {
         constexpr int s = CV(S);
         if constexpr (s < NF) {
             if constexpr (s % SPC == 0) st.template next<(s / SPC + PAR0) & 1>();
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                a[s % (D + 1)][u] = st.template frag<(s / SPC + PAR0) & 1>((s % SPC) * U + u);
+            a[s % (D + 1)] = st.template frag<(s / SPC + PAR0) & 1>(s % SPC);
         }
         if constexpr (s >= D) {
             constexpr int f = s - D;
             constexpr int p = f / PF, w = f % PF, k = w / RBP, r = w % RBP;
-            if constexpr (!OV) {
-                if constexpr (w == 0) load_bias(std::integral_constant<int, p>{});
-            } else {
-                if constexpr (p == 0 && w == 0) load_bias(std::integral_constant<int, 0>{});
-                if constexpr (p + 1 < NP && w == PF - LEAD) load_bias(std::integral_constant<int, p + 1>{});
-            }
+            if constexpr (w == 0)
+                sfor<RBP>([&](auto R) {
+                    const f32x16 b = bias_frag(bias + 32 * (RBP * p + CV(R)), g);
+                    sfor<CB>([&](auto C) { acc[p & 1][CV(R)][CV(C)] = b; });
+                });
             sfor<CB>([&](auto C) {
-                u32x4 bk[U];
-                sfor<U>([&](auto V) { bk[CV(V)] = getB(std::integral_constant<int, k * U + CV(V)>{}, C); });
-                acc[p & 1][r][CV(C)] = M::mma(a[f % (D + 1)], bk, acc[p & 1][r][CV(C)], sa);
+                const u32x4 bk = getB(std::integral_constant<int, k>{}, C);
+                acc[p & 1][r][CV(C)] = M::mma(&a[f % (D + 1)], &bk, acc[p & 1][r][CV(C)], 127);
             });
-            if constexpr (!OV) {
-                if constexpr (w == PF - 1) epilogue(std::integral_constant<int, p>{});
-            } else {
-                if constexpr (p >= 1 && w == DEL) epilogue(std::integral_constant<int, p - 1>{});
-                if constexpr (p == NP - 1 && w == PF - 1) epilogue(std::integral_constant<int, p>{});
-            }
+            if constexpr (w == PF - 1)
+                sfor<RBP>([&](auto R) {
+                    sfor<CB>([&](auto C) { emit_relu(acc[p & 1][CV(R)][CV(C)], out, (p * RBP + CV(R)) * 2, CV(C)); });
+                });
         }
         __builtin_amdgcn_sched_barrier(0x6);
     });
     // a layer of an odd number of chunks is padded to an even one (unless
     // the stream omits that padding)
-    constexpr int CH = (NF * U + kChunkFrags - 1) / kChunkFrags;
+    constexpr int CH = (NF + kChunkFrags - 1) / kChunkFrags;
     if constexpr (PADDED && (CH & 1)) st.template next<(CH + PAR0) & 1>();
 }
 
@@ -497,7 +389,7 @@ __device__ __forceinline__ uint32_t relu_bf16x2(float lo, float hi) {
 // A 256 -> 256 bf16 ReLU layer on 16x16x32 steps: four passes of four 16-row
 // tiles (one 32 KiB chunk each), each over eight K steps of 32, for the two
 // 16-column tiles, so a pass runs eight independent accumulation chains.  As
-// in hidden_layer, passes alternate between two accumulator sets and the LDS
+// in first_layer, passes alternate between two accumulator sets and the LDS
 // reads run kFragAhead fragments ahead.  G: the lane group (lane / 16).
 // getB(e, 0) returns entry e (16x16 step e / 2, tile e % 2) of the input;
 // out receives the output in the same form.
@@ -947,8 +839,8 @@ constexpr int kCdfClass = 2 * 16;   // a ray's sample classes follow its (depth,
 static_assert(kCdfClass + 16 <= kCdfRayStride, "a ray's samples fit its row");
 static_assert(kCdfWaveFloats >= 8 * 64 * 4 && kCdfWaveFloats % 4 == 0, "a pass's values fit a wave's region");
 
-// PR: network precision (layout.h Precision; an fp8 network keeps its first
-// layers and heads in bf16).  CB: 32-ray column blocks per wave.  NW: waves
+// The main kernel of bf16 networks.  PR: network precision (layout.h
+// Precision).  CB: 32-ray column blocks per wave.  NW: waves
 // per workgroup.  OCC: waves per SIMD the register budget is sized for (with
 // OCC * 4 > NW several workgroups share a CU).  NCAP: capacity of the top-N
 // list (top-N) or of the sample arrays (CDF).  PLACE: sample placement.
@@ -956,7 +848,7 @@ static_assert(kCdfWaveFloats >= 8 * 64 * 4 && kCdfWaveFloats % 4 == 0, "a pass's
 template <int PR, int CB, int NW, int OCC, int NCAP, int PLACE, int DIN>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 render_kernel(const RenderArgs a) {
-    static_assert(PR != kF32, "fp32 networks run on rows_kernel.h");
+    static_assert(PR == kBF16 && CB == 1, "fp32 networks run on rows_kernel.h, fp8 ones on rows_fp8_kernel.h");
     constexpr int FP = kBF16;   // first layers, heads, features
     using P = Prec<FP>;
     constexpr int E = P::E;
@@ -964,7 +856,6 @@ render_kernel(const RenderArgs a) {
     // positions input (always fp32 steps, 8 K each)
     constexpr int KS_D0 = DIN == kDinEncoded ? kDKPad / (2 * E) : kPKPad / (2 * Prec<kF32>::E);
     constexpr int KS_H = kHidden / (2 * E);       // heads: 16
-    constexpr int KS_HID = ksteps(PR, kHidden);   // hidden layers: 16 | 4
     constexpr int KS_S0 = kSKPad / (2 * E);       // 4
     constexpr int KS_SK = kSkipKPad / (2 * E);    // 2
 
@@ -1062,54 +953,37 @@ render_kernel(const RenderArgs a) {
 #pragma unroll
         for (int ks = 0; ks < KS_SK; ++ks) skip[ks][cb] = P::pack(fs + E * ks);
     }
-    // a 16x16 shading head reads the skip as one K step of its two tiles
-    if constexpr (hid16(PR)) swap16(skip[0][0], skip[1][0]);
+    // the 16x16 shading head reads the skip as one K step of its two tiles
+    swap16(skip[0][0], skip[1][0]);
     lds_barrier();  // bias_s and bins_s visible
 
     // ---- depth-oracle network
-    // Layers alternate h0 -> h1 -> h0; h0 holds the input of the next layer
-    // (an fp8 layer's input takes the first 2 KS_HID entries).
+    // Layers alternate h0 -> h1 -> h0; h0 holds the input of the next layer.
     u32x4 h0[KS_H][CB], h1[KS_H][CB];
     auto g0 = [&](auto K, auto C) { return h0[CV(K)][CV(C)]; };
     auto g1 = [&](auto K, auto C) { return h1[CV(K)][CV(C)]; };
-    // six 256 -> 256 ReLU layers whose biases start at bias_l0 and whose fp8
-    // weight scales start at ws; the last one feeds a head in FP
-    // (PAR: slot parity of the first chunk; every hidden layer streams an
-    // even number of chunks, so it holds for all six)
-    // BACK: whether the output returns to the 32x32 layout (the depth head
-    // needs it; the shading head of a 16x16 network reads the 16x16 one)
-    auto hidden6 = [&](auto PAR, BiasAt bias_l0, const int32_t* ws, auto BACK) {
+    // six 256 -> 256 ReLU layers whose biases start at bias_l0, on 16x16 steps:
+    // the first layer's output changes layout on the way in, the last hidden
+    // layer's on the way out to a 32x32 head (BACK: the depth head needs it; the
+    // shading head reads the 16x16 layout).  PAR: slot parity of the first chunk
+    // (every hidden layer streams an even number of chunks, so it holds for all
+    // six).
+    auto hidden6 = [&](auto PAR, BiasAt bias_l0, auto BACK) {
         constexpr int Q = CV(PAR);
-        if constexpr (PR == kFP8) {
-            for (int l = 0; l < 2; ++l) {
-                hidden_layer<kFP8, CB, KS_HID, kFP8, Q>(st, g, bias_l0 + 256 * (2 * l), g0, h1, ws[2 * l]);
-                hidden_layer<kFP8, CB, KS_HID, kFP8, Q>(st, g, bias_l0 + 256 * (2 * l + 1), g1, h0, ws[2 * l + 1]);
-            }
-            hidden_layer<kFP8, CB, KS_HID, kFP8, Q>(st, g, bias_l0 + 256 * 4, g0, h1, ws[4]);
-            hidden_layer<FP, CB, KS_HID, kFP8, Q>(st, g, bias_l0 + 256 * 5, g1, h0, ws[5]);
-        } else if constexpr (hid16(PR)) {
-            // 16x16 steps: the first layer's output changes layout on the way
-            // in, the last hidden layer's on the way out to a 32x32 head
-            const int G = lane >> 4;
-            swap_layouts(h0);
-            for (int l = 0; l < 3; ++l) {
-                hidden_layer16<Q>(st, G, bias_l0 + 256 * (2 * l), g0, h1);
-                hidden_layer16<Q>(st, G, bias_l0 + 256 * (2 * l + 1), g1, h0);
-            }
-            if constexpr (CV(BACK)) swap_layouts(h0);
-        } else {
-            for (int l = 0; l < 3; ++l) {
-                hidden_layer<PR, CB, KS_HID, PR, Q>(st, g, bias_l0 + 256 * (2 * l), g0, h1);
-                hidden_layer<PR, CB, KS_HID, PR, Q>(st, g, bias_l0 + 256 * (2 * l + 1), g1, h0);
-            }
+        const int G = lane >> 4;
+        swap_layouts(h0);
+        for (int l = 0; l < 3; ++l) {
+            hidden_layer16<Q>(st, G, bias_l0 + 256 * (2 * l), g0, h1);
+            hidden_layer16<Q>(st, G, bias_l0 + 256 * (2 * l + 1), g1, h0);
         }
+        if constexpr (CV(BACK)) swap_layouts(h0);
     };
     static_assert(layer_chunks(PR, kHiddenL, 128) % 2 == 0, "hidden layers keep the slot parity");
     {
         auto gin = [&](auto K, auto C) { return din[CV(K)][CV(C)]; };
-        hidden_layer<PR, CB, KS_D0, DIN == kDinEncoded ? FP : kF32>(st, g, BiasAt{bias_s, 0}, gin, h0);
+        first_layer<CB, KS_D0, DIN == kDinEncoded ? FP : kF32>(st, g, BiasAt{bias_s, 0}, gin, h0);
     }
-    hidden6(std::integral_constant<int, 0>{}, BiasAt{bias_s, 256}, a.wscale + 1, std::true_type{});
+    hidden6(std::integral_constant<int, 0>{}, BiasAt{bias_s, 256}, std::true_type{});
     // Head of the depth network: B / 64 passes of 64 classes (32 * kRbPerPass).
     const int npass = a.B / (32 * kRbPerPass);
     constexpr int PASS_FRAGS = KS_H * kRbPerPass;
@@ -1435,10 +1309,9 @@ render_kernel(const RenderArgs a) {
         static_assert((S0C + HIDC + HEADC) % 2 == 0, "a sample's chunks keep the slot parity");
         {
             auto gs = [&](auto K, auto C) { return sin_[CV(K)][CV(C)]; };
-            hidden_layer<PR, CB, KS_S0, FP, 0, layer_even_padded(kSFirst)>(st, g, BiasAt{bias_s, s_bias}, gs, h0);
+            first_layer<CB, KS_S0, FP, 0, layer_even_padded(kSFirst)>(st, g, BiasAt{bias_s, s_bias}, gs, h0);
         }
-        hidden6(std::integral_constant<int, S0C & 1>{}, BiasAt{bias_s, s_bias + 256}, a.wscale + 9,
-                std::integral_constant<bool, !hid16(PR)>{});
+        hidden6(std::integral_constant<int, S0C & 1>{}, BiasAt{bias_s, s_bias + 256}, std::false_type{});
         // compositing of one sample from its head outputs (r, g, b, sigma)
         auto composite = [&](auto C, float hr, float hg, float hb, float hs) {
             constexpr int cb = CV(C);
@@ -1455,22 +1328,10 @@ render_kernel(const RenderArgs a) {
             Dp[cb] += wgt * tk[cb];
             T[cb] *= exp_neg<false>(tau);
         };
-        if constexpr (hid16(PR)) {
-            head16<kChunkFrags * ((S0C + HIDC) & 1)>(st, lane >> 4, BiasAt{bias_s, s_bias + 7 * 256}, h0, skip,
-                                                     [&](const f32x4& o) {
-                                                         composite(std::integral_constant<int, 0>{}, o[0], o[1], o[2], o[3]);
-                                                     });
-        } else {
-            auto gh = [&](auto K, auto C) {
-                if constexpr (CV(K) < KS_H) return h0[CV(K)][CV(C)];
-                else return skip[CV(K) - KS_H][CV(C)];
-            };
-            run_pass<FP, CB, KS_H + KS_SK, 1, kChunkFrags * ((S0C + HIDC) & 1)>(
-                st, g, BiasAt{bias_s, s_bias + 7 * 256}, gh, [&](auto R, auto C, const f32x16& acc) {
-                    // lanes of group 0 hold rows 0..3 = (r, g, b, sigma) in registers 0..3
-                    composite(C, acc[0], acc[1], acc[2], acc[3]);
-                });
-        }
+        head16<kChunkFrags * ((S0C + HIDC) & 1)>(st, lane >> 4, BiasAt{bias_s, s_bias + 7 * 256}, h0, skip,
+                                                 [&](const f32x4& o) {
+                                                     composite(std::integral_constant<int, 0>{}, o[0], o[1], o[2], o[3]);
+                                                 });
     }
     st.finish();  // no copy into LDS may outlive the workgroup
 
