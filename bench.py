@@ -24,6 +24,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 157.3, "fp8": 5000.0}   # MI355X dense peaks
+# fp32 networks run on the bf16 matrix cores, six products for one
+FP32_NETWORK_PEAK_TFLOPS = MFMA_PEAK_TFLOPS["bf16"] / 6
 HBM_PEAK_GBS = 8000.0
 
 # HBM KiB per dispatch from two rocprofv3 --pmc runs (FETCH_SIZE, then
@@ -301,10 +303,11 @@ def main():
     ms_step = wall * 1e3 / args.steps
     value = rays / (ms_step * 1e-3) / 1e6
     d_in = depth_in_folded(wl.depth_input)
-    sweeps = 2 if wl.select == "cdf" and wl.n_bins > 128 else 1
+    sweeps = 2 if wl.select == "cdf" and wl.n_bins > 128 and wl.precision == "bf16" else 1
     flop_launch = algorithmic_flop_per_ray(wl.N, wl.n_bins, d_in) * rays
     achieved = flop_launch / (avg_kern_ms * 1e-3) / 1e12
-    peak = (mixed_peak(wl.N, wl.n_bins, d_in) if wl.precision == "fp8" else MFMA_PEAK_TFLOPS[wl.precision])
+    peak = (mixed_peak(wl.N, wl.n_bins, d_in) if wl.precision == "fp8"
+            else FP32_NETWORK_PEAK_TFLOPS if wl.precision == "fp32" else MFMA_PEAK_TFLOPS[wl.precision])
     paper_mrays = 400 * 400 / 22e-3 / 1e6   # 22 ms per 400x400 frame, N = 4
     kib = args.traffic_kib
     if kib is not None:
@@ -340,6 +343,7 @@ def main():
                                           / (avg_kern_ms * 1e-3) / 1e12 / peak, 4),
                      **({"peak_note": "fp8 hidden layers at 5000, bf16 first layers and heads at 2500, "
                                       "combined by their share of the work"} if wl.precision == "fp8" else {}),
+                     **({"peak_note": "2500 bf16 / 6 products per fp32 product"} if wl.precision == "fp32" else {}),
                      "traffic": traffic,
                      "kernel": f"render_kernel<{wl.precision}>", "kernel_ms": round(avg_kern_ms, 4),
                      "kernel_ms_median": round(float(np.median(kern_ms)), 4)},
@@ -348,7 +352,8 @@ def main():
         # the measured ceiling: a register-fed MFMA loop on random operands
         line["roofline"]["mfma_loop"] = {"achieved": round(loop, 2), "frac_of_peak":
                                          round(loop / MFMA_PEAK_TFLOPS[wl.precision], 4)}
-        if wl.precision != "fp8":   # the fp8 network mixes fp8 and bf16 layers
+        # the fp8 network mixes fp8 and bf16 layers, the fp32 network runs on bf16 MFMAs
+        if wl.precision == "bf16":
             line["roofline"]["frac_of_mfma_loop"] = round(achieved / loop, 4)
     if not args.no_cpu:
         line["cpu_baseline"] = cpu_baseline(wl, weights, poses, args.cpu_sample or default_cpu_sample(wl))

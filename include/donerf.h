@@ -86,9 +86,7 @@ typedef enum donerf_select {
                                        coordinate of Eq. 3), its CDF inverted at
                                        u_i = (i + 0.5)/N; sample i's width is the
                                        depth extent of the slice [i/N, (i+1)/N].
-                                       fp32 arithmetic; above 128 classes the
-                                       depth head runs twice (class sums, then
-                                       the values the targets fall in)       */
+                                       fp32 arithmetic                        */
 } donerf_select;
 
 typedef enum donerf_depth_input {

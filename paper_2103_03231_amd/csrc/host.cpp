@@ -63,8 +63,9 @@ size_t blob_w_count(int l, int n_bins, int depth_input) {
 
 bool bins_supported(int B) { return B >= 64 && B <= 256 && B % 64 == 0; }
 
-// Inverse-CDF placement over more classes than fit in registers: the kernel
-// runs the depth head twice, and the depth stream carries its chunks twice.
+// Inverse-CDF placement over more classes than fit in registers: the main bf16
+// kernel runs the depth head twice, and the depth stream of a bf16 network
+// carries its chunks twice.
 bool wide_cdf(const donerf_cfg& c) { return c.select == DONERF_SELECT_CDF && c.n_bins > 128; }
 
 int validate_cfg(const donerf_cfg* c) {
@@ -535,7 +536,7 @@ int donerf_create(const donerf_cfg* cfg, const float* weights, size_t n_weights,
             pack_layer(fp, prec, kind, kind == kHiddenL ? l % 8 - 1 : -1, B, weights + off, s, frags);
         }
         (l < 8 ? n_d_chunks : n_s_chunks) += layer_chunks(prec, kind, B);
-        if (l == 7 && wide_cdf(*cfg) && prec != kF32) {
+        if (l == 7 && wide_cdf(*cfg) && prec == kBF16) {
             pack_layer(fp, prec, kind, -1, B, weights + off, s, frags);
             n_d_chunks += layer_chunks(prec, kind, B);
         }

@@ -50,7 +50,8 @@ constexpr int kMaxPosesPerLaunch = 32;
 #endif
 constexpr int kRbPerPass = DONERF_RB_PER_PASS;  // 32-row blocks per accumulator pass
 
-// Arithmetic of a layer's MFMA steps (bool true/false convert to bf16/fp32).
+// Precision of a network, and the arithmetic of a layer's MFMA steps (kF32: the
+// folded positions layer only; fp32 networks: rows32_* below).
 enum Precision { kF32 = 0, kBF16 = 1, kFP8 = 2 };
 
 // K elements per lane per step, K per step, 1 KiB units per step, bytes per
@@ -149,9 +150,10 @@ DN_HD constexpr int p_feature(int ks, int g, int e) {
 }
 
 // Sample placement and depth-network input of a render variant.  kPlaceCdf
-// keeps a ray's B <= 128 class values in registers; kPlaceCdfWide (B = 192,
-// 256) runs the depth head twice, so the depth stream of such a network
-// carries the head's chunks twice.
+// has B <= 128 class values per ray, kPlaceCdfWide 192 or 256.  render_kernel.h
+// keeps the former in registers and runs the depth head twice for the latter, so
+// the depth stream of such a bf16 network carries the head's chunks twice; the
+// other kernels pass the values through LDS.
 enum Placement { kPlaceTopN = 0, kPlaceCdf = 1, kPlaceCdfWide = 2 };
 enum DepthInput { kDinEncoded = 0, kDinPositions = 1 };
 
@@ -192,7 +194,7 @@ DN_HD constexpr int layer_frags(int net, int kind, int n_bins) {
 // to an even number of chunks, so that each starts in slot 0 of the two-slot
 // LDS stream and the slot of every chunk is known at compile time.  The
 // shading network's first layer and head are not: a sample's chunks add up to
-// an even number (bf16 1 + 24 + 1, fp8 1 + 12 + 1, fp32 2 + 48 + 2), so every
+// an even number (bf16 1 + 24 + 1, fp8 1 + 12 + 1), so every
 // sample still starts in slot 0 and its layers' slots stay compile-time
 // constants, and the two padding chunks per sample it saves are two barriers
 // and two copies (0.45 % of the bf16 and 1.1 % of the fp8 step).

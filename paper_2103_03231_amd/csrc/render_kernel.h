@@ -1,4 +1,5 @@
-// render_kernel.h - the fused DONeRF per-ray kernel for gfx950 (MI355X).
+// render_kernel.h - the fused DONeRF per-ray kernel for gfx950 (MI355X): the main
+// kernel of bf16 networks, and the parts every render kernel shares.
 //
 // One workgroup renders a tile of rays: ray generation and unification
 // (Sec. 5.2), the depth-network input (encoded, Eq. 2, or the unencoded
