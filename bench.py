@@ -33,8 +33,8 @@ HBM_PEAK_GBS = 8000.0
 # 256 MiB copy (FETCH_SIZE reads half the bytes moved: x2; WRITE_SIZE exact:
 # x1), per workload, valid only for the kernel sources they were taken with.
 MEASURED_TRAFFIC = {
-    "frame400_n4_bf16": {"sources_sha256_16": "592a453b4efe06fb", "fetch_kib": 7307.0 * 2, "write_kib": 11760.0},
-    "targets400_b128_k5_z5": {"sources_sha256_16": "80e10b6e7a011a43", "fetch_kib": 9065.9 * 2, "write_kib": 400000.0},
+    "frame400_n4_bf16": {"sources_sha256_16": "bce60d8ed4b622b7", "fetch_kib": 7307.0 * 2, "write_kib": 11760.0},
+    "targets400_b128_k5_z5": {"sources_sha256_16": "48282f28eaf42fb1", "fetch_kib": 9065.9 * 2, "write_kib": 400000.0},
 }
 # the sources (and the build script, whose flags shape the code) each
 # measured kernel is built from
