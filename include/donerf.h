@@ -225,6 +225,22 @@ int donerf_render_debug(donerf_t* h, const float* cam_poses, int32_t P, int32_t 
                         int32_t* out_bins, float* out_scores, float* out_samples);
 
 /*
+ * How donerf_render cuts a call, for testing; needs no device.  On a device of
+ * n_cu compute units (1..2^16), launch `launch` (0, 1, ...) of the call takes
+ *   out[0]  poses (0 past the last launch, and the rest then 0)
+ *   out[1]  rays per tile
+ *   out[2]  tiles rendered whole, by one workgroup each
+ *   out[3]  tiles split by samples
+ *   out[4]  workgroups per split tile
+ *   out[5]  threads per workgroup
+ * Errors: E_INVALID_ARG, E_NONFINITE and E_UNSUPPORTED for a cfg that
+ * donerf_create refuses; E_INVALID_ARG (NULL out, n_cu or launch out of range,
+ * sizes that donerf_render refuses).
+ */
+int donerf_debug_plan(const donerf_cfg* cfg, int32_t n_cu, int32_t P, int32_t H, int32_t W, int32_t N,
+                      int32_t launch, int32_t* out);
+
+/*
  * Run the device top-N selection on given scores, for testing.
  *   scores   device, rays x B fp32
  *   out_idx  device, rays x N int32: the N classes with the highest scores,

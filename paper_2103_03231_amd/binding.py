@@ -38,8 +38,8 @@ MAX_SAMPLES = 16
 # Every function include/donerf.h declares.
 EXPORTS = ("donerf_weight_count", "donerf_create", "donerf_destroy", "donerf_set_stream",
            "donerf_render", "donerf_render_static_scratch", "donerf_render_debug", "donerf_targets",
-           "donerf_debug_topn", "donerf_debug_bins", "donerf_debug_mfma_peak", "donerf_status_str",
-           "donerf_last_error")
+           "donerf_debug_plan", "donerf_debug_topn", "donerf_debug_bins", "donerf_debug_mfma_peak",
+           "donerf_status_str", "donerf_last_error")
 
 
 class DonerfLibraryMissing(RuntimeError):
@@ -109,6 +109,8 @@ def lib():
         L.donerf_render_debug.restype = ctypes.c_int
         L.donerf_targets.argtypes = [vp, vp, i32, i32, i32, i32, i32, vp]
         L.donerf_targets.restype = ctypes.c_int
+        L.donerf_debug_plan.argtypes = [ctypes.POINTER(donerf_cfg), i32, i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
+        L.donerf_debug_plan.restype = ctypes.c_int
         L.donerf_debug_topn.argtypes = [vp, vp, i32, i32, vp]
         L.donerf_debug_topn.restype = ctypes.c_int
         L.donerf_debug_bins.argtypes = [vp, fp, fp, fp]
@@ -182,6 +184,15 @@ def donerf_render_debug(h, poses, P, H, W, N, out_rgb_ptr, out_depth_ptr=None,
 
 def donerf_targets(h, depth_ptr, P, H, W, K, Z, out_ptr) -> None:
     _check(lib().donerf_targets(h, depth_ptr, P, H, W, K, Z, out_ptr))
+
+
+def donerf_debug_plan(cfg: Config, P, H, W, N, launch=0, n_cu=256) -> dict:
+    """How a render of these sizes is cut: launch `launch`'s part, {} past the last one."""
+    out = (ctypes.c_int32 * 6)()
+    c = cfg.to_c()
+    _check(lib().donerf_debug_plan(ctypes.byref(c), n_cu, P, H, W, N, launch, out))
+    keys = ("poses", "tile_rays", "n_full", "n_split", "split", "threads")
+    return dict(zip(keys, out)) if out[0] else {}
 
 
 def donerf_debug_topn(h, scores_ptr, rays, N, out_idx_ptr) -> None:

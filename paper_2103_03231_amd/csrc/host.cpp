@@ -68,6 +68,10 @@ bool bins_supported(int B) { return B >= 64 && B <= 256 && B % 64 == 0; }
 // carries its chunks twice.
 bool wide_cdf(const donerf_cfg& c) { return c.select == DONERF_SELECT_CDF && c.n_bins > 128; }
 
+int precision_of(const donerf_cfg& c) {
+    return c.precision == DONERF_FP8 ? kFP8 : c.precision == DONERF_BF16 ? kBF16 : kF32;
+}
+
 int validate_cfg(const donerf_cfg* c) {
     if (!c) return fail(DONERF_E_INVALID_ARG, "cfg is NULL");
     const float fs[] = {c->near_dist, c->far_dist, c->fov_x_deg, c->centre[0], c->centre[1],
@@ -322,16 +326,21 @@ int check_device(int* dev_out) {
     return DONERF_OK;
 }
 
+int validate_sizes(const donerf_cfg& c, int32_t P, int32_t H, int32_t W, int32_t N) {
+    if (P < 1 || H < 1 || W < 1) return fail(DONERF_E_INVALID_ARG, "P, H and W must be >= 1");
+    if (N < 1 || N > c.n_max || N > c.n_bins) return fail(DONERF_E_INVALID_ARG, "N must lie in [1, n_max]");
+    if ((int64_t)P * H * W >= ((int64_t)1 << 31)) return fail(DONERF_E_INVALID_ARG, "P*H*W must be < 2^31");
+    if ((int64_t)H * W > (1 << 24)) return fail(DONERF_E_INVALID_ARG, "H*W must be <= 2^24");
+    return DONERF_OK;
+}
+
 int validate_render(const donerf_t* h, const float* poses, int32_t P, int32_t H, int32_t W, int32_t N,
                     const float* out_rgb) {
     if (!h) return fail(DONERF_E_INVALID_ARG, "handle is NULL");
     if (!poses) return fail(DONERF_E_INVALID_ARG, "cam_poses is NULL");
     if (!out_rgb) return fail(DONERF_E_INVALID_ARG, "out_rgb is NULL");
-    if (P < 1 || H < 1 || W < 1) return fail(DONERF_E_INVALID_ARG, "P, H and W must be >= 1");
-    if (N < 1 || N > h->cfg.n_max || N > h->cfg.n_bins)
-        return fail(DONERF_E_INVALID_ARG, "N must lie in [1, n_max]");
-    if ((int64_t)P * H * W >= ((int64_t)1 << 31)) return fail(DONERF_E_INVALID_ARG, "P*H*W must be < 2^31");
-    if ((int64_t)H * W > (1 << 24)) return fail(DONERF_E_INVALID_ARG, "H*W must be <= 2^24");
+    const int rc = validate_sizes(h->cfg, P, H, W, N);
+    if (rc) return rc;
     for (int64_t k = 0; k < (int64_t)P * 12; ++k)
         if (!finite(poses[k])) return fail(DONERF_E_NONFINITE, "cam_poses holds a NaN or Inf");
     return DONERF_OK;
@@ -364,7 +373,7 @@ const TileCost kTileCosts[] = {
 };
 constexpr float kCombineCost = 4.0f;   // the combine launch of a split tail
 
-TailPlan plan_tail(const donerf_t* h, uint32_t total_rays, int32_t N) {
+TailPlan plan_tail(int prec, uint32_t n_cu, uint32_t total_rays, int32_t N) {
     // For a tile size: full rounds of per_cu workgroups per CU run as they are.
     // The r tiles of a last, partial round are split by samples, each over up to
     // as many workgroups as one (or per_cu) per CU allows; every part recomputes
@@ -373,17 +382,17 @@ TailPlan plan_tail(const donerf_t* h, uint32_t total_rays, int32_t N) {
     TailPlan best{};
     float best_t = 0.0f;
     for (const TileCost& c : kTileCosts) {
-        if (c.prec != h->prec) continue;
-        const uint32_t round = (uint32_t)h->n_cu * c.per_cu;
+        if (c.prec != prec) continue;
+        const uint32_t round = n_cu * c.per_cu;
         const uint32_t tiles = total_rays / c.rays + (total_rays % c.rays != 0);
         const uint32_t full = tiles / round * round, rem = tiles - full;
         const float t_full = (float)(full / round) * (c.depth + (float)N * c.sample);
         for (uint32_t u = c.per_cu; u >= 1; --u) {
-            uint32_t split = rem ? (uint32_t)h->n_cu * u / rem : 1;
+            uint32_t split = rem ? n_cu * u / rem : 1;
             if (split > (uint32_t)N) split = (uint32_t)N;
             if (split < 1) split = 1;
             const uint32_t part = ((uint32_t)N + split - 1) / split;   // samples of a split part
-            const float load = rem * split <= (uint32_t)h->n_cu ? c.alone : 1.0f;
+            const float load = rem * split <= n_cu ? c.alone : 1.0f;
             const float t = t_full + (rem ? load * (c.depth + (float)part * c.sample) + (split > 1 ? kCombineCost : 0.0f)
                                           : 0.0f);
             if (best.tile_rays == 0 || t < best_t) {
@@ -400,6 +409,24 @@ size_t tail_floats(const TailPlan& t) {
     return t.split > 1 ? (size_t)5 * t.rem * t.tile_rays * t.split : 0;
 }
 
+// The next launch of a call: of the poses_left poses at most np, and their plan.
+struct LaunchPlan {
+    int np;
+    TailPlan tail;
+};
+
+// A launch holds fewer poses than the kernel arguments do where its work-items
+// would pass the dispatch packet's 32-bit grid size: 32 views of 2^24 rays in
+// fp32 are 2^23 tiles of 512 threads.  One view of 2^24 rays always fits.
+LaunchPlan plan_launch(int prec, uint32_t n_cu, int32_t poses_left, size_t hw, int32_t N) {
+    int np = poses_left < kMaxPosesPerLaunch ? poses_left : kMaxPosesPerLaunch;
+    for (;; --np) {
+        const TailPlan t = plan_tail(prec, n_cu, (uint32_t)(np * hw), N);
+        const uint64_t groups = t.n_full + (uint64_t)t.rem * t.split;
+        if (np == 1 || groups * (uint64_t)tile_threads(prec, (int)t.tile_rays) <= UINT32_MAX) return LaunchPlan{np, t};
+    }
+}
+
 // partial: split-tail scratch of partial_cap floats (the handle's buffer, or
 // the static scratch).
 int render_impl(donerf_t* h, const float* poses, int32_t P, int32_t H, int32_t W, int32_t N, float* out_rgb,
@@ -409,9 +436,10 @@ int render_impl(donerf_t* h, const float* poses, int32_t P, int32_t H, int32_t W
     if (rc) return rc;
     const size_t hw = (size_t)H * W;
     // every launch's scratch need is known before the first one is enqueued
-    for (int32_t p0 = 0; p0 < P; p0 += kMaxPosesPerLaunch) {
-        const int np = P - p0 < kMaxPosesPerLaunch ? P - p0 : kMaxPosesPerLaunch;
-        const size_t need = tail_floats(plan_tail(h, (uint32_t)(np * hw), N));
+    LaunchPlan lp;
+    for (int32_t p0 = 0; p0 < P; p0 += lp.np) {
+        lp = plan_launch(h->prec, (uint32_t)h->n_cu, P - p0, hw, N);
+        const size_t need = tail_floats(lp.tail);
         if (need > partial_cap)
             return fail(DONERF_E_UNSUPPORTED, "the split tail needs " + std::to_string(need) +
                                                   " floats of scratch, " + std::to_string(partial_cap) +
@@ -447,8 +475,9 @@ int render_impl(donerf_t* h, const float* poses, int32_t P, int32_t H, int32_t W
     a.dmax = c.far_dist;
     a.log2_span1 = (float)std::log2((double)c.far_dist - (double)c.near_dist + 1.0);
     const int place = c.select != DONERF_SELECT_CDF ? kPlaceTopN : wide_cdf(c) ? kPlaceCdfWide : kPlaceCdf;
-    for (int32_t p0 = 0; p0 < P; p0 += kMaxPosesPerLaunch) {
-        const int np = P - p0 < kMaxPosesPerLaunch ? P - p0 : kMaxPosesPerLaunch;
+    for (int32_t p0 = 0; p0 < P; p0 += lp.np) {
+        lp = plan_launch(h->prec, (uint32_t)h->n_cu, P - p0, hw, N);
+        const int np = lp.np;
         a.n_poses = np;
         a.total_rays = (uint32_t)(np * hw);
         std::memcpy(a.poses, poses + (size_t)p0 * 12, sizeof(float) * 12 * np);
@@ -457,7 +486,7 @@ int render_impl(donerf_t* h, const float* poses, int32_t P, int32_t H, int32_t W
         a.out_bins = out_bins ? out_bins + (size_t)p0 * hw * N : nullptr;
         a.out_scores = out_scores ? out_scores + (size_t)p0 * hw * c.n_bins : nullptr;
         a.out_samples = out_samples ? out_samples + (size_t)p0 * hw * N * 2 : nullptr;
-        const TailPlan tp = plan_tail(h, a.total_rays, N);
+        const TailPlan& tp = lp.tail;
         a.n_full = tp.n_full;
         a.split = (int32_t)tp.split;
         a.tile_rays = (int32_t)tp.tile_rays;
@@ -508,7 +537,7 @@ int donerf_create(const donerf_cfg* cfg, const float* weights, size_t n_weights,
     rc = check_device(&dev);
     if (rc) return rc;
 
-    const int prec = cfg->precision == DONERF_FP8 ? kFP8 : cfg->precision == DONERF_BF16 ? kBF16 : kF32;
+    const int prec = precision_of(*cfg);
     const int B = cfg->n_bins;
     const bool positions = cfg->depth_input == DONERF_DEPTH_POSITIONS;
     std::vector<float> bounds, centres, widths;
@@ -638,6 +667,32 @@ int donerf_render_debug(donerf_t* h, const float* cam_poses, int32_t P, int32_t 
     g_err.clear();
     return render_impl(h, cam_poses, P, H, W, N, out_rgb, out_depth, out_bins, out_scores, out_samples,
                        h ? h->partial : nullptr, h ? (size_t)5 * 256 * (size_t)h->n_cu : 0);
+}
+
+int donerf_debug_plan(const donerf_cfg* cfg, int32_t n_cu, int32_t P, int32_t H, int32_t W, int32_t N,
+                      int32_t launch, int32_t* out) {
+    g_err.clear();
+    int rc = validate_cfg(cfg);
+    if (rc) return rc;
+    if (!out) return fail(DONERF_E_INVALID_ARG, "NULL buffer");
+    if (n_cu < 1 || n_cu > (1 << 16)) return fail(DONERF_E_INVALID_ARG, "n_cu must lie in [1, 2^16]");
+    if (launch < 0) return fail(DONERF_E_INVALID_ARG, "launch must be >= 0");
+    rc = validate_sizes(*cfg, P, H, W, N);
+    if (rc) return rc;
+    const int prec = precision_of(*cfg);
+    for (int k = 0; k < 6; ++k) out[k] = 0;
+    for (int32_t p0 = 0; p0 < P; --launch) {
+        const LaunchPlan lp = plan_launch(prec, (uint32_t)n_cu, P - p0, (size_t)H * W, N);
+        if (launch == 0) {
+            const TailPlan& t = lp.tail;
+            const int32_t v[6] = {lp.np, (int32_t)t.tile_rays, (int32_t)t.n_full, (int32_t)t.rem, (int32_t)t.split,
+                                  tile_threads(prec, (int)t.tile_rays)};
+            std::memcpy(out, v, sizeof v);
+            break;
+        }
+        p0 += lp.np;
+    }
+    return DONERF_OK;
 }
 
 int donerf_debug_topn(donerf_t* h, const float* scores, int32_t rays, int32_t N, int32_t* out_idx) {

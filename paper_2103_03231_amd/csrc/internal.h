@@ -73,8 +73,15 @@ constexpr int kBf16Occ = DONERF_BF16_OCC;
 // the network).
 constexpr int kF32CB = 2;
 constexpr int kF8CB = 4;
+// Waves per workgroup of the fp8 main kernel and of rows_kernel.h's.
+constexpr int kF8Waves = 4;
+constexpr int kRowWaves = 8;
 inline int rays_per_block(int prec) {
     return prec == kF32 ? 32 * kF32CB : prec == kFP8 ? 32 * kF8CB : kBf16NW * 32 * kBf16CB;
+}
+// Threads of the workgroup that renders a tile of tile_rays rays.
+inline int tile_threads(int prec, int tile_rays) {
+    return 64 * (prec == kF32 || tile_rays != rays_per_block(prec) ? kRowWaves : prec == kFP8 ? kF8Waves : kBf16NW);
 }
 
 // Launches a.n_full whole tiles plus n_split_tiles tiles split a.split ways.

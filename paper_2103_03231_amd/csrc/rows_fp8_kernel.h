@@ -39,8 +39,6 @@
 namespace donerf {
 namespace {
 
-constexpr int kF8Waves = 4;
-
 template <int NCAP, int PLACE, int DIN>
 struct RowsFp8 {
     static constexpr int R = 32 * kF8CB, CB = kF8CB;

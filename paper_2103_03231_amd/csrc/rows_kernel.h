@@ -39,7 +39,6 @@
 namespace donerf {
 namespace {
 
-constexpr int kRowWaves = 8;
 constexpr int kRowThreads = 64 * kRowWaves;
 
 // A layer's 1 KiB fragments as the kernel addresses them, counted from the

@@ -1,0 +1,66 @@
+"""How a render call is cut into launches and tiles, without a GPU: every ray is
+rendered by one tile, every launch fits the 32-bit grid of the dispatch packet,
+and its split tail fits the scratch."""
+import random
+
+import pytest
+
+from paper_2103_03231_amd import binding as b
+
+PREC = {"fp32": b.FP32, "bf16": b.BF16, "fp8": b.FP8}
+SCRATCH = 5 * 256 * 256   # floats of the split tail's scratch at 256 compute units
+
+
+def plan(precision, P, H, W, N, n_cu=256, **cfg):
+    c = b.Config(precision=PREC[precision], n_max=16, **cfg)
+    out = []
+    while True:
+        p = b.donerf_debug_plan(c, P, H, W, N, launch=len(out), n_cu=n_cu)
+        if not p:
+            return out
+        out.append(p)
+
+
+def check(launches, P, H, W, n_cu=256):
+    assert sum(p["poses"] for p in launches) == P
+    for p in launches:
+        assert 1 <= p["poses"] <= 32
+        tiles = -(-p["poses"] * H * W // p["tile_rays"])
+        assert p["n_full"] + p["n_split"] == tiles, p
+        groups = p["n_full"] + p["n_split"] * p["split"]
+        assert groups * p["threads"] < 2 ** 32, p
+        if p["split"] > 1:
+            assert 5 * p["n_split"] * p["split"] * p["tile_rays"] <= SCRATCH * n_cu // 256, p
+
+
+# fp32 tiles of 64 rays are rendered by 512 threads: 32 views of 2^24 rays are
+# 2^32 work-items, one more than a launch can have
+@pytest.mark.parametrize("P,H,W", [(32, 4096, 4096), (127, 4096, 4096), (32, 1, (1 << 24) - 1), (35, 4095, 4097),
+                                   (1, 4096, 4096), (33, 4000, 4000)])
+@pytest.mark.parametrize("precision", PREC)
+def test_launches_fit_the_grid_at_the_size_limits(precision, P, H, W):
+    for N in (1, 4, 16):
+        check(plan(precision, P, H, W, N), P, H, W)
+
+
+@pytest.mark.parametrize("precision", PREC)
+def test_plans_cover_every_ray_within_the_scratch(precision):
+    rng = random.Random(7)
+    for _ in range(400):
+        P = rng.choice([1, 1, 2, 5, 32, 33])
+        H, W = (int(2 ** rng.uniform(0, 10.5)) for _ in range(2))
+        N, n_cu = rng.randrange(1, 17), rng.choice([256, 256, 304, 64, 1])
+        kw = {"n_bins": rng.choice([64, 128, 192, 256]), "select": rng.choice([b.SELECT_TOPN, b.SELECT_CDF]),
+              "depth_input": rng.choice([b.DEPTH_ENCODED, b.DEPTH_POSITIONS])}
+        check(plan(precision, P, H, W, N, n_cu, **kw), P, H, W, n_cu)
+
+
+def test_plan_refuses_what_render_refuses():
+    c = b.Config(n_max=4)
+    for args in ((0, 4, 4, 4), (1, 4, 4, 5), (1, 4, 4, 0), (1, 4097, 4096, 4), (128, 4096, 4096, 4)):
+        with pytest.raises(b.DonerfError) as e:
+            b.donerf_debug_plan(c, *args)
+        assert e.value.status == b.E_INVALID_ARG
+    with pytest.raises(b.DonerfError) as e:
+        b.donerf_debug_plan(b.Config(n_bins=100), 1, 4, 4, 4)
+    assert e.value.status == b.E_UNSUPPORTED
