@@ -52,9 +52,11 @@ typedef enum donerf_status {
 } donerf_status;
 
 typedef enum donerf_precision {
-    DONERF_FP32 = 0, /* fp32 weights, features and activations: each the exact
-                        sum of three bf16 values, products from six bf16 MFMA
-                        products with fp32 accumulation                      */
+    DONERF_FP32 = 0, /* fp32 weights, features and activations: each the sum
+                        of three bf16 values, exact from 2^-110 on (below, to
+                        2^-134), products from six bf16 MFMA products with fp32
+                        accumulation.  Infinite activations act as in fp32; one
+                        of 0x1.ffp127 or more (3.396e38) counts as infinite   */
     DONERF_BF16 = 1, /* bf16 weights, features and hidden activations (RNE),
                         fp32 accumulation, fp32 scores, heads, compositing;
                         sine, cosine, exp and reciprocal of the encoding and

@@ -160,12 +160,14 @@ int fp8_scale(const float* W, size_t n) {
     return s;
 }
 
-float bf16_value(float x) {
-    const uint32_t u = (uint32_t)to_bf16(x) << 16;
+float bf16_float(uint16_t h) {
+    const uint32_t u = (uint32_t)h << 16;
     float f;
     std::memcpy(&f, &u, 4);
     return f;
 }
+
+float bf16_value(float x) { return bf16_float(to_bf16(x)); }
 
 // Folds the first depth layer of the positions input (256 x (6 + 3 B) over
 // [u', r, p_0, ..., p_{B-1}], p_k = u_c + (c_k / d_max) r) into 256 x 9 over
@@ -278,6 +280,13 @@ void pack_layer(int prec, int net, int kind, int hidx, int n_bins, const float* 
             }
 }
 
+// The leading one of a weight's three bf16 values: x rounded to nearest, or cut
+// off where that would round a finite x to infinity.
+uint16_t top_bf16(float x) {
+    const uint16_t h = to_bf16(x);
+    return (h & 0x7FFFu) == 0x7F80u ? (uint16_t)(h - 1) : h;
+}
+
 // Append one layer of an fp32 network: every weight as three bf16 values in
 // the fragment order of layout.h rows32_layer_frags.
 void pack_rows32(int kind, int n_bins, const float* W, std::vector<uint8_t>& dst) {
@@ -299,8 +308,8 @@ void pack_rows32(int kind, int n_bins, const float* W, std::vector<uint8_t>& dst
                         if (col[e] < 0) continue;
                         float x = w[col[e]];
                         for (int p = 0; p < 3; ++p) {
-                            h[p][e] = to_bf16(x);
-                            x -= bf16_value(x);   // exact: x and its bf16 share their leading bits
+                            h[p][e] = p ? to_bf16(x) : top_bf16(x);
+                            x -= bf16_float(h[p][e]);   // exact: x and its bf16 share their leading bits
                         }
                     }
                     uint8_t* frag = out + (size_t)(rb * KS + ks) * 3 * kFragBytes + (g * rows + r) * 16;

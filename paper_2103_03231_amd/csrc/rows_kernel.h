@@ -53,9 +53,11 @@ DN_HD constexpr int rows_layer_frags(int net, int kind, int n_bins) {
 
 // x = p0 + p1 + p2 exactly, each a bf16: x rounded to nearest, then what is
 // left, then the rest (both differences are exact and need at most 16 and 8
-// bits).  Rounding rather than truncating halves the second plane, gives it
-// either sign, and so makes the dropped products smaller and unbiased.  Eight
-// values become one 16-byte unit per plane.
+// bits; below 2^-110 the last bits of the rest fall under bf16's subnormals).
+// Rounding rather than truncating halves the second plane, gives it either sign,
+// and so makes the dropped products smaller and unbiased.  Eight values become
+// one 16-byte unit per plane.  An infinity (and a finite value that rounds to one,
+// from 0x1.ffp127 on) is an infinite p0 and NaN in the others; NaN is three NaN.
 __device__ __forceinline__ void split3(const float* f, u32x4 (&o)[3]) {
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -68,6 +70,21 @@ __device__ __forceinline__ void split3(const float* f, u32x4 (&o)[3]) {
             y -= __uint_as_float(h & 0xFFFF0000u);
         }
     }
+}
+
+// A sum from its two accumulators.  Non-finite operands make hi what the fp32
+// sum would be (infinite, or NaN) and lo anything, and a hi that overflows may
+// meet an infinite lo of the other sign: held to finite values (v_med3_f32
+// gives a finite one for NaN), lo leaves such a hi as it is.  The instruction per
+// value costs 1 % (400 x 400, N = 4: 2,969 -> 3,002 us; 32 x 32: 72.2 -> 72.8);
+// looking for such a lo over the wave first (v_maximum3_f32, a branch) costs 0.6 %
+// and 1.9 %.
+template <class V>
+__device__ __forceinline__ V join(V hi, V lo) {
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(V) / 4); ++i)
+        hi[i] = hi[i] + __builtin_amdgcn_fmed3f(lo[i], -3.402823466e38f, 3.402823466e38f);
+    return hi;
 }
 
 // The six products of one K step: a[], b[] hold the three planes.
@@ -280,7 +297,7 @@ struct RowsRender {
         });
         if constexpr (F32)
 #pragma unroll
-            for (int j = 0; j < NC; ++j) acc[j] = acc[j] + lo[j];
+            for (int j = 0; j < NC; ++j) acc[j] = join(acc[j], lo[j]);
     }
 
     // first layers: units in 32x32 order (2 ks + g)
@@ -839,7 +856,7 @@ struct RowsRender {
                         if constexpr (F32) mma_split16(hw[u], bv, acc, lo);
                         else acc = mma16(hw[u][0], bv[0], acc);
                     }
-                    if constexpr (F32) acc = acc + lo;
+                    if constexpr (F32) acc = join(acc, lo);
                     h0 = acc[0], h1 = acc[1], h2 = acc[2], h3 = acc[3];
                 } else {
                     f32x16 acc = bias_frag(BiasAt{sh.bias, s_bias + 7 * 256}, g);
