@@ -377,7 +377,7 @@ struct TileCost {
 };
 const TileCost kTileCosts[] = {
     {kF32, 32 * kF32CB, 1, 75.0f, 62.0f, 1.0f}, {kF32, 32, 1, 43.0f, 34.5f, 1.0f},
-    {kBF16, 256, 1, 40.0f, 31.0f, 1.0f},        {kBF16, 64, 1, 18.5f, 12.2f, 1.0f}, {kBF16, 32, 1, 15.0f, 7.8f, 1.0f},
+    {kBF16, 32 * kBf16NW * kBf16CB, 1, 40.0f, 31.0f, 1.0f},        {kBF16, 64, 1, 18.5f, 12.2f, 1.0f}, {kBF16, 32, 1, 15.0f, 7.8f, 1.0f},
     {kFP8, 32 * kF8CB, 2, 32.0f, 21.5f, 0.66f}, {kFP8, 64, 1, 15.5f, 7.6f, 1.0f},   {kFP8, 32, 1, 12.0f, 5.5f, 1.0f},
 };
 constexpr float kCombineCost = 4.0f;   // the combine launch of a split tail

@@ -8,6 +8,8 @@ import pytest
 from paper_2103_03231_amd import binding as b
 
 PREC = {"fp32": b.FP32, "bf16": b.BF16, "fp8": b.FP8}
+# every tile a precision has a kernel for, and that kernel's threads
+TILES = {"fp32": {64: 512, 32: 512}, "bf16": {256: 512, 64: 512, 32: 512}, "fp8": {128: 256, 64: 512, 32: 512}}
 SCRATCH = 5 * 256 * 256   # floats of the split tail's scratch at 256 compute units
 
 
@@ -21,10 +23,11 @@ def plan(precision, P, H, W, N, n_cu=256, **cfg):
         out.append(p)
 
 
-def check(launches, P, H, W, n_cu=256):
+def check(precision, launches, P, H, W, n_cu=256):
     assert sum(p["poses"] for p in launches) == P
     for p in launches:
         assert 1 <= p["poses"] <= 32
+        assert TILES[precision][p["tile_rays"]] == p["threads"], p
         tiles = -(-p["poses"] * H * W // p["tile_rays"])
         assert p["n_full"] + p["n_split"] == tiles, p
         groups = p["n_full"] + p["n_split"] * p["split"]
@@ -40,7 +43,7 @@ def check(launches, P, H, W, n_cu=256):
 @pytest.mark.parametrize("precision", PREC)
 def test_launches_fit_the_grid_at_the_size_limits(precision, P, H, W):
     for N in (1, 4, 16):
-        check(plan(precision, P, H, W, N), P, H, W)
+        check(precision, plan(precision, P, H, W, N), P, H, W)
 
 
 @pytest.mark.parametrize("precision", PREC)
@@ -52,7 +55,7 @@ def test_plans_cover_every_ray_within_the_scratch(precision):
         N, n_cu = rng.randrange(1, 17), rng.choice([256, 256, 304, 64, 1])
         kw = {"n_bins": rng.choice([64, 128, 192, 256]), "select": rng.choice([b.SELECT_TOPN, b.SELECT_CDF]),
               "depth_input": rng.choice([b.DEPTH_ENCODED, b.DEPTH_POSITIONS])}
-        check(plan(precision, P, H, W, N, n_cu, **kw), P, H, W, n_cu)
+        check(precision, plan(precision, P, H, W, N, n_cu, **kw), P, H, W, n_cu)
 
 
 def test_plan_refuses_what_render_refuses():
