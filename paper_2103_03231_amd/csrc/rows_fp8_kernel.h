@@ -301,8 +301,13 @@ struct RowsFp8 {
     }
 
     // The lane's indices, through an asm the compiler cannot see through: LDS
-    // addresses made from them are made again in each phase instead of being
-    // held in registers (and spilled) across the tile.
+    // addresses made from them are made again in each phase, and in each stage of
+    // a sample, instead of being held in registers (and spilled) across the tile.
+    // Without that in the samples, the ray made again, the dumps before them and
+    // weight pointers to global memory (opaque), inverse CDF spilled 24 to 76
+    // registers and every wait in the layers was a wait for all loads: 131,072
+    // rays, N = 16, inverse CDF, 192 classes 804 -> 754 us; top-N, 128 classes
+    // 763 -> 741 us; 5 x 400 x 400, N = 4 1,379 -> 1,347 us.
     __device__ __forceinline__ void set_lane(int l) {
         asm volatile("" : "+v"(l));
         lane = l;
@@ -354,8 +359,9 @@ struct RowsFp8 {
         // ---- the lane's ray, the depth-network input, the direction skip
         auto rl = [&]() { return 32 * wave + col; };    // ray within the tile
         auto rid = [&]() { return ray0 + (uint32_t)rl(); };
-        const Ray ray = camera_ray(a, rid() < a.total_rays ? rid() : a.total_rays - 1);
+        auto lane_ray = [&]() { return camera_ray(a, rid() < a.total_rays ? rid() : a.total_rays - 1); };
         {
+            const Ray ray = lane_ray();
             float ou[3], v[3];
             unify(a, ray, ou);
             v[0] = (ou[0] - a.cx) / a.dmax;
@@ -499,16 +505,32 @@ struct RowsFp8 {
             }
         };
 
+        if (part == 0 && (a.out_bins || a.out_samples))
+            for (int k = 0; k < a.N; ++k) {
+                int c;
+                float t, d;
+                sample(k, c, t, d);
+                if (g == 0 && rid() < a.total_rays) {
+                    const size_t at = (size_t)rid() * a.N + k;
+                    if (a.out_bins) a.out_bins[at] = c;
+                    if (a.out_samples) {
+                        a.out_samples[2 * at] = t;
+                        a.out_samples[2 * at + 1] = d;
+                    }
+                }
+            }
+
         // ---- shading network per sample
         set_lane(lane);
         lds_barrier();   // the depth network's biases and the scores are read
         for (int k = 64 * wave + lane; k < 7 * 256 + 32; k += NT) sh.bias[k] = a.bias[7 * 256 + k];
         sfor<kHeld>([&](auto I) { ring[CV(I)] = s0[CV(I) * 64 + lane]; });
+        const Ray ray = lane_ray();   // made again: not held (and spilled) across the depth network
         float T = 1.0f, Cr = 0.0f, Cg = 0.0f, Cb = 0.0f, Dp = 0.0f;
         for (int k = k_begin; k < k_end; ++k) {
             // keeps the samples' equal weight loads inside the loop
-            const u32x4 *s0k = s0, *shk = shd, *hk = shead;
-            asm volatile("" : "+s"(s0k), "+s"(shk), "+s"(hk));
+            const u32x4 *s0k = opaque(s0), *shk = opaque(shd), *hk = opaque(shead);
+            set_lane(lane);
             int c;
             float tk, dk;
             sample(k, c, tk, dk);
@@ -525,9 +547,12 @@ struct RowsFp8 {
                 for (int ks = 0; ks < KS_S0; ++ks) sh.pool[(2 * ks + g) * R + rl()] = Prec<kBF16>::pack(f + 8 * ks);
             }
             lds_barrier();
+            set_lane(lane);
             first_layer<KS_S0, 0>(s0k, shk, 0);
             lds_barrier();
+            set_lane(lane);
             hidden6(shk, s0k, 1, 256, a.wscale + 9);
+            set_lane(lane);
             // head: the wave's own 32 columns, one row block
             f32x16 acc = bias_frag(BiasAt{sh.bias, 7 * 256}, g);
             u32x4 hw[KS_H + 2];
@@ -557,19 +582,6 @@ struct RowsFp8 {
         set_lane(lane);
         const uint32_t ro = rid();
         const bool valid = ro < a.total_rays;
-        if (a.out_bins || a.out_samples)
-            for (int k = 0; k < a.N; ++k) {
-                int c;
-                float t, d;
-                sample(k, c, t, d);
-                if (g == 0 && valid && part == 0) {
-                    if (a.out_bins) a.out_bins[(size_t)ro * a.N + k] = c;
-                    if (a.out_samples) {
-                        a.out_samples[((size_t)ro * a.N + k) * 2 + 0] = t;
-                        a.out_samples[((size_t)ro * a.N + k) * 2 + 1] = d;
-                    }
-                }
-            }
         if (g == 0 && valid) {
             if (nsplit > 1) {
                 float* q = a.partial + ((size_t)(tile_local * R + rl()) * nsplit + part) * 5;

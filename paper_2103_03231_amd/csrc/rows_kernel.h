@@ -49,6 +49,17 @@ DN_HD constexpr int rows_layer_frags(int net, int kind, int n_bins) {
     return net == kF32 ? rows32_layer_frags(kind, n_bins) : layer_chunks(net, kind, n_bins) * kChunkFrags;
 }
 
+// A pointer to weights that the compiler cannot see through: loads that every
+// sample makes again are loop-invariant, and hoisted out they would be held in
+// registers throughout.  It passes the asm as a pointer to global memory: from a
+// generic one the loads would be flat_load, which take a 64-bit address in VGPRs
+// each, count as LDS accesses too and so make every wait a wait for all.
+__device__ __forceinline__ const u32x4* opaque(const u32x4* p) {
+    auto q = (const __attribute__((address_space(1))) u32x4*)p;
+    asm volatile("" : "+s"(q));
+    return (const u32x4*)q;
+}
+
 // ------------------------------------------------------------------ fp32 as three bf16
 
 // x = p0 + p1 + p2 exactly, each a bf16: x rounded to nearest, then what is

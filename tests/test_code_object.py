@@ -1,6 +1,7 @@
 """Resource use of the built gfx950 kernels, read from the library's code
 object without a GPU: every render kernel fits one workgroup's LDS, and the
-top-N render kernels read neither the dispatch packet nor scratch memory.
+top-N render kernels and those of fp8 networks read neither the dispatch packet
+nor scratch memory.
 
 A kernel that indexes a small per-lane array at a computed index gets that
 array moved into a per-thread LDS block, whose address is built from the
@@ -116,3 +117,14 @@ def test_topn_kernels_read_no_dispatch_packet_and_no_scratch(kernels):
     for params, (lds, scratch, dispatch) in topn:
         assert not dispatch, ("reads the dispatch packet", params)
         assert scratch == 0, ("spills to scratch", params, scratch)
+
+
+def test_fp8_kernels_read_no_dispatch_packet_and_no_scratch(kernels):
+    """Inverse-CDF placement included: a ray's depths and slice ends stay in
+    registers through a kernel that fills most of them."""
+    fp8 = [(p, d) for p, d in _render(kernels) if p[0] == 2]
+    assert len(fp8) == 3 * 3 * 2   # placements x sample capacities x depth inputs
+    for params, (lds, scratch, dispatch) in fp8:
+        assert scratch == 0, ("spills to scratch", params, scratch)
+        assert not dispatch, ("reads the dispatch packet", params)
+        assert lds <= LDS_PER_CU // 2, ("two workgroups share a CU", params, lds)
