@@ -786,11 +786,8 @@ struct RowsRender {
 #pragma unroll
             for (int ks = 0; ks < KS_S0; ++ks) s0w[ks] = s0[at(kOneMap, ks) * 64 + lane];
         for (int k = k_begin; k < k_end; ++k) {
-            // Loads of weights that every sample reads again are loop-invariant,
-            // and hoisted out they would be held in registers throughout:
-            // pointers the compiler cannot see through keep them here.
-            const u32x4 *s0k = s0, *shk = shd, *hk = shead;
-            asm volatile("" : "+s"(s0k), "+s"(shk), "+s"(hk));
+            // keeps the samples' equal weight loads inside the loop
+            const u32x4 *s0k = opaque(s0), *shk = opaque(shd), *hk = opaque(shead);
             // the last head read buffer 1 (its only buffer, if there is one)
             if constexpr (NBUF == 1) lds_barrier();
             // tasks from the last wave down: the first waves run the head
