@@ -363,46 +363,71 @@ struct TailPlan {
     uint32_t tile_rays, n_full, rem, split;
 };
 
-// Measured time of one round of tiles of a size, per_cu of them on every CU, in
-// microseconds: depth network with selection and launch, and each sample of the
-// shading network; alone: the share of it that a round of at most one tile per
-// CU takes.  The first entry of a precision is its main kernel's tile, the
-// others rows_kernel.h's; fits of renders of 992 to 160,000 rays at N = 1, 4 and
-// 16, B = 128.  A smaller tile costs more per ray but its round is shorter, so it
-// wins where the larger tiles leave CUs idle.
+// Measured time of tiles of a size, per_cu of them on every CU, in microseconds.
+// A round of N samples takes
+//   depth + pos + per_b B / 64 + (cdf N / 4, or topn per 4 entries of the list)
+//         + N sample:
+// the depth network with the launch, what the positions input takes longer (its
+// first layer runs on fp32 MFMAs), the head, the placement, the shading network.  A last round on part of the chip takes a share of that: alone if no
+// CU has two tiles, otherwise light + (1 - light) times the share of tiles there
+// (fewer busy CUs clock higher).  Splitting the last round costs combine +
+// combine_part per part.  The first entry of a precision is its main kernel's
+// tile, the others rows_kernel.h's.
+//
+// The fp8 entries are fits over 1,170 random calls (300 to 260,000 rays, N = 1 to
+// 16, every B, both placements and depth inputs), each timed with every tile and
+// several splits: the plan taken is 0.1 % from the best of those on average and
+// 7 % at most; with one depth, sample and combine figure per tile it was 30 % at
+// most, and ten of the calls ran 2 to 10 % slower than on tiles of 256 rays.  The
+// bf16 and fp32 entries are fits of top-N renders at B = 128, 992 to 160,000 rays:
+// over 900 and 360 such calls 0.5 and 0.8 % from the best on average, and none
+// slower than on the tiles of 256 and 128 rays alone.
 struct TileCost {
     int prec;
     uint32_t rays, per_cu;
-    float depth, sample, alone;
+    float depth, pos, per_b, cdf, topn, sample, alone, light, combine, combine_part;
 };
 const TileCost kTileCosts[] = {
-    {kF32, 32 * kF32CB, 1, 75.0f, 62.0f, 1.0f}, {kF32, 32, 1, 43.0f, 34.5f, 1.0f},
-    {kBF16, 32 * kBf16NW * kBf16CB, 1, 40.0f, 31.0f, 1.0f},        {kBF16, 64, 1, 18.5f, 12.2f, 1.0f}, {kBF16, 32, 1, 15.0f, 7.8f, 1.0f},
-    {kFP8, 32 * kF8CB, 2, 32.0f, 21.5f, 0.66f}, {kFP8, 64, 1, 15.5f, 7.6f, 1.0f},   {kFP8, 32, 1, 12.0f, 5.5f, 1.0f},
+    {kF32, 32 * kF32CB, 1, 75.0f, 0.0f, 0.0f, 0.0f, 0.0f, 62.0f, 1.0f, 1.0f, 4.0f, 0.0f},
+    {kF32, 32, 1, 43.0f, 0.0f, 0.0f, 0.0f, 0.0f, 34.5f, 1.0f, 1.0f, 4.0f, 0.0f},
+    {kBF16, 32 * kBf16NW * kBf16CB, 1, 40.0f, 0.0f, 0.0f, 0.0f, 0.0f, 31.0f, 1.0f, 1.0f, 4.0f, 0.0f},
+    {kBF16, 64, 1, 18.5f, 0.0f, 0.0f, 0.0f, 0.0f, 12.2f, 1.0f, 1.0f, 4.0f, 0.0f},
+    {kBF16, 32, 1, 15.0f, 0.0f, 0.0f, 0.0f, 0.0f, 7.8f, 1.0f, 1.0f, 4.0f, 0.0f},
+    {kFP8, 32 * kF8CB, 2, 21.3f, 2.07f, 4.51f, 4.22f, 1.87f, 18.86f, 0.67f, 0.73f, 1.89f, 0.54f},
+    {kFP8, 64, 1, 11.5f, 0.48f, 1.02f, 1.66f, 1.36f, 6.65f, 0.92f, 0.92f, 1.57f, 0.41f},
+    {kFP8, 32, 1, 10.4f, 0.56f, 0.58f, 1.32f, 1.12f, 4.84f, 0.95f, 0.95f, 1.70f, 0.35f},
 };
-constexpr float kCombineCost = 4.0f;   // the combine launch of a split tail
 
-TailPlan plan_tail(int prec, uint32_t n_cu, uint32_t total_rays, int32_t N) {
+TailPlan plan_tail(const donerf_cfg& cfg, uint32_t n_cu, uint32_t total_rays, int32_t N) {
     // For a tile size: full rounds of per_cu workgroups per CU run as they are.
     // The r tiles of a last, partial round are split by samples, each over up to
-    // as many workgroups as one (or per_cu) per CU allows; every part recomputes
-    // the depth network, and a combine pass composites the parts.  The size and
-    // split with the smallest estimate are taken, the main kernel's on a tie.
+    // as many workgroups as a round allows; every part recomputes the depth
+    // network, and a combine pass composites the parts.  The size and split with
+    // the smallest estimate are taken, on a tie the main kernel's and the most
+    // parts.
+    const int prec = precision_of(cfg);
     TailPlan best{};
     float best_t = 0.0f;
     for (const TileCost& c : kTileCosts) {
         if (c.prec != prec) continue;
+        const bool main_tile = c.rays == (uint32_t)rays_per_block(prec);
+        const float list = N <= 4 ? 1.0f : N <= 8 && main_tile ? 2.0f : 4.0f;   // rows_kernel.h: 4 or 16 entries
+        const float depth = c.depth + (cfg.depth_input == DONERF_DEPTH_POSITIONS ? c.pos : 0.0f) +
+                            c.per_b * (float)(cfg.n_bins / 64) +
+                            (cfg.select == DONERF_SELECT_CDF ? c.cdf * (float)N / 4.0f : c.topn * list);
         const uint32_t round = n_cu * c.per_cu;
         const uint32_t tiles = total_rays / c.rays + (total_rays % c.rays != 0);
         const uint32_t full = tiles / round * round, rem = tiles - full;
-        const float t_full = (float)(full / round) * (c.depth + (float)N * c.sample);
-        for (uint32_t u = c.per_cu; u >= 1; --u) {
-            uint32_t split = rem ? n_cu * u / rem : 1;
-            if (split > (uint32_t)N) split = (uint32_t)N;
-            if (split < 1) split = 1;
+        const float t_full = (float)(full / round) * (depth + (float)N * c.sample);
+        uint32_t split = rem ? round / rem : 1;
+        if (split > (uint32_t)N) split = (uint32_t)N;
+        for (; split >= 1; --split) {
             const uint32_t part = ((uint32_t)N + split - 1) / split;   // samples of a split part
-            const float load = rem * split <= n_cu ? c.alone : 1.0f;
-            const float t = t_full + (rem ? load * (c.depth + (float)part * c.sample) + (split > 1 ? kCombineCost : 0.0f)
+            const uint32_t parts = rem * split;
+            const float load = c.per_cu > 1 && parts <= n_cu ? c.alone
+                                                             : c.light + (1.0f - c.light) * (float)parts / (float)round;
+            const float t = t_full + (rem ? load * (depth + (float)part * c.sample) +
+                                                (split > 1 ? c.combine + c.combine_part * (float)split : 0.0f)
                                           : 0.0f);
             if (best.tile_rays == 0 || t < best_t) {
                 best = TailPlan{c.rays, split > 1 ? full : tiles, split > 1 ? rem : 0, split};
@@ -427,12 +452,12 @@ struct LaunchPlan {
 // A launch holds fewer poses than the kernel arguments do where its work-items
 // would pass the dispatch packet's 32-bit grid size: 32 views of 2^24 rays in
 // fp32 are 2^23 tiles of 512 threads.  One view of 2^24 rays always fits.
-LaunchPlan plan_launch(int prec, uint32_t n_cu, int32_t poses_left, size_t hw, int32_t N) {
+LaunchPlan plan_launch(const donerf_cfg& cfg, uint32_t n_cu, int32_t poses_left, size_t hw, int32_t N) {
     int np = poses_left < kMaxPosesPerLaunch ? poses_left : kMaxPosesPerLaunch;
     for (;; --np) {
-        const TailPlan t = plan_tail(prec, n_cu, (uint32_t)(np * hw), N);
+        const TailPlan t = plan_tail(cfg, n_cu, (uint32_t)(np * hw), N);
         const uint64_t groups = t.n_full + (uint64_t)t.rem * t.split;
-        if (np == 1 || groups * (uint64_t)tile_threads(prec, (int)t.tile_rays) <= UINT32_MAX) return LaunchPlan{np, t};
+        if (np == 1 || groups * (uint64_t)tile_threads(precision_of(cfg), (int)t.tile_rays) <= UINT32_MAX) return LaunchPlan{np, t};
     }
 }
 
@@ -447,7 +472,7 @@ int render_impl(donerf_t* h, const float* poses, int32_t P, int32_t H, int32_t W
     // every launch's scratch need is known before the first one is enqueued
     LaunchPlan lp;
     for (int32_t p0 = 0; p0 < P; p0 += lp.np) {
-        lp = plan_launch(h->prec, (uint32_t)h->n_cu, P - p0, hw, N);
+        lp = plan_launch(h->cfg, (uint32_t)h->n_cu, P - p0, hw, N);
         const size_t need = tail_floats(lp.tail);
         if (need > partial_cap)
             return fail(DONERF_E_UNSUPPORTED, "the split tail needs " + std::to_string(need) +
@@ -485,7 +510,7 @@ int render_impl(donerf_t* h, const float* poses, int32_t P, int32_t H, int32_t W
     a.log2_span1 = (float)std::log2((double)c.far_dist - (double)c.near_dist + 1.0);
     const int place = c.select != DONERF_SELECT_CDF ? kPlaceTopN : wide_cdf(c) ? kPlaceCdfWide : kPlaceCdf;
     for (int32_t p0 = 0; p0 < P; p0 += lp.np) {
-        lp = plan_launch(h->prec, (uint32_t)h->n_cu, P - p0, hw, N);
+        lp = plan_launch(h->cfg, (uint32_t)h->n_cu, P - p0, hw, N);
         const int np = lp.np;
         a.n_poses = np;
         a.total_rays = (uint32_t)(np * hw);
@@ -688,14 +713,13 @@ int donerf_debug_plan(const donerf_cfg* cfg, int32_t n_cu, int32_t P, int32_t H,
     if (launch < 0) return fail(DONERF_E_INVALID_ARG, "launch must be >= 0");
     rc = validate_sizes(*cfg, P, H, W, N);
     if (rc) return rc;
-    const int prec = precision_of(*cfg);
     for (int k = 0; k < 6; ++k) out[k] = 0;
     for (int32_t p0 = 0; p0 < P; --launch) {
-        const LaunchPlan lp = plan_launch(prec, (uint32_t)n_cu, P - p0, (size_t)H * W, N);
+        const LaunchPlan lp = plan_launch(*cfg, (uint32_t)n_cu, P - p0, (size_t)H * W, N);
         if (launch == 0) {
             const TailPlan& t = lp.tail;
             const int32_t v[6] = {lp.np, (int32_t)t.tile_rays, (int32_t)t.n_full, (int32_t)t.rem, (int32_t)t.split,
-                                  tile_threads(prec, (int)t.tile_rays)};
+                                  tile_threads(precision_of(*cfg), (int)t.tile_rays)};
             std::memcpy(out, v, sizeof v);
             break;
         }

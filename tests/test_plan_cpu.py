@@ -67,3 +67,31 @@ def test_plan_refuses_what_render_refuses():
     with pytest.raises(b.DonerfError) as e:
         b.donerf_debug_plan(b.Config(n_bins=100), 1, 4, 4, 4)
     assert e.value.status == b.E_UNSUPPORTED
+
+
+# Microseconds of one call of an fp8 network on an MI355X, by (rays per tile,
+# workgroups per tile of the last round): every tile and several splits timed.
+MEASURED_FP8 = [
+    ("cdf", "positions", 256, 4422, 7, {(32, 1): 48.2, (64, 1): 61.8, (64, 3): 41.3, (128, 1): 119.3, (128, 3): 73.8,
+                                        (128, 7): 54.2}),
+    ("cdf", "encoded", 192, 7310, 16, {(32, 1): 92.6, (64, 1): 119.8, (64, 2): 76.1, (128, 1): 229.3, (128, 2): 135.8,
+                                       (128, 4): 92.3, (128, 8): 90.9}),
+    ("cdf", "encoded", 192, 12100, 9, {(32, 1): 114.1, (32, 2): 98.5, (64, 1): 77.5, (128, 1): 142.4, (128, 2): 99.7,
+                                       (128, 5): 86.4}),
+    ("cdf", "positions", 64, 5550, 5, {(32, 1): 37.8, (64, 1): 47.1, (64, 2): 37.8, (128, 1): 85.1, (128, 2): 63.1,
+                                       (128, 5): 41.6}),
+    ("cdf", "positions", 64, 39800, 8, {(32, 1): 257.4, (64, 1): 209.3, (64, 2): 187.8, (128, 1): 172.4}),
+    ("topn", "positions", 64, 5852, 16, {(32, 1): 90.0, (64, 1): 119.0, (64, 2): 71.0, (128, 1): 216.6, (128, 2): 122.7,
+                                         (128, 5): 76.9, (128, 11): 77.6}),
+    ("topn", "encoded", 128, 24964, 4, {(32, 1): 116.4, (32, 4): 104.3, (64, 1): 78.6, (128, 1): 69.7, (128, 2): 64.8}),
+    ("topn", "encoded", 192, 25440, 4, {(32, 1): 120.1, (32, 4): 107.2, (64, 1): 81.7, (128, 1): 75.3, (128, 2): 71.5}),
+    ("topn", "encoded", 64, 5929, 4, {(32, 1): 30.5, (64, 1): 38.2, (64, 2): 28.9, (128, 1): 67.7, (128, 2): 45.9,
+                                      (128, 4): 35.1}),
+]
+
+
+@pytest.mark.parametrize("select,din,B,rays,N,us", MEASURED_FP8)
+def test_fp8_plan_is_near_the_fastest_measured(select, din, B, rays, N, us):
+    (p,) = plan("fp8", 1, 1, rays, N, n_bins=B, select=b.SELECT_CDF if select == "cdf" else b.SELECT_TOPN,
+                depth_input=b.DEPTH_POSITIONS if din == "positions" else b.DEPTH_ENCODED)
+    assert us[p["tile_rays"], p["split"]] <= 1.05 * min(us.values()), p
