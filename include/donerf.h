@@ -243,7 +243,9 @@ int donerf_debug_plan(const donerf_cfg* cfg, int32_t n_cu, int32_t P, int32_t H,
                       int32_t launch, int32_t* out);
 
 /*
- * Run the device top-N selection on given scores, for testing.
+ * Run the device top-N selection on given scores, for testing: the code that a
+ * render of that many rays on this handle would select with (kernels of
+ * different tile sizes split a ray's classes over 2, 8 or 16 lanes).
  *   scores   device, rays x B fp32
  *   out_idx  device, rays x N int32: the N classes with the highest scores,
  *            ties broken towards the lower class index, +0 and -0 equal,

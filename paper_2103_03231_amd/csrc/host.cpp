@@ -734,7 +734,9 @@ int donerf_debug_topn(donerf_t* h, const float* scores, int32_t rays, int32_t N,
     if (!scores || !out_idx) return fail(DONERF_E_INVALID_ARG, "NULL buffer");
     if (rays < 1) return fail(DONERF_E_INVALID_ARG, "rays must be >= 1");
     if (N < 1 || N > h->cfg.n_max || N > h->cfg.n_bins) return fail(DONERF_E_INVALID_ARG, "N out of range");
-    hipError_t e = launch_topn(h->prec != kF32, ncap_for(N), scores, rays, N, h->cfg.n_bins, out_idx, h->stream);
+    const TailPlan t = plan_tail(h->cfg, (uint32_t)h->n_cu, (uint32_t)rays, N);
+    hipError_t e = launch_topn(h->prec, (int)t.tile_rays, ncap_for(N), scores, rays, N, h->cfg.n_bins, out_idx,
+                               h->stream);
     if (e != hipSuccess) return hip_fail(e, "topn launch");
     return DONERF_OK;
 }

@@ -115,8 +115,9 @@ constexpr int kMaxDevices = 64;
 // device; looked up once per device, then cached.
 hipError_t static_scratch_address(int device, float** out);
 hipError_t launch_softmax_rows(float* scores, uint32_t rows, int B, hipStream_t stream);
-hipError_t launch_topn(bool bf16_layout, int ncap, const float* scores, int32_t rays,
-                       int32_t N, int32_t B, int32_t* out_idx, hipStream_t stream);
+// The selection that the kernel of a tile runs, on given scores.
+hipError_t launch_topn(int prec, int tile_rays, int ncap, const float* scores, int32_t rays, int32_t N, int32_t B,
+                       int32_t* out_idx, hipStream_t stream);
 
 // Register-fed MFMA loop (kernels.hip): workgroups x 4 waves, four
 // independent 32 x 32 chains of `iters` steps per wave in precision prec;

@@ -4,7 +4,7 @@
 // launches to the per-variant translation units.
 #include <mutex>
 
-#include "render_kernel.h"
+#include "rows_kernel.h"
 
 namespace donerf {
 namespace {
@@ -45,35 +45,48 @@ __global__ void softmax_rows_kernel(float* s, uint32_t rows, int B) {
     for (int k = 0; k < B; ++k) x[k] = expf(x[k] - m) / sum;
 }
 
-// The render kernel's selection on given scores: each lane pushes its classes
-// in the render kernel's register order, then merges with its partner lane.
-template <int CB, int NCAP>
+// The selection of the main bf16 and fp8 kernels on given scores: a ray's
+// classes are split by blocks of four between lanes l and l + 32, which push
+// them in ascending order and merge their lists.
+template <int NCAP>
 __global__ void __launch_bounds__(256) topn_kernel(const float* scores, int32_t rays, int32_t N, int32_t B,
                                                    int32_t* out) {
     const int lane = threadIdx.x & 63;
     const int g = lane >> 5;
     const int col = lane & 31;
-    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    sfor<CB>([&](auto C) {
-        const int32_t r = wave * 32 * CB + 32 * CV(C) + col;
-        const bool valid = r < rays;
-        const float* row = scores + (size_t)(valid ? r : rays - 1) * B;
-        TopList<NCAP> t;
-        t.init();
-        for (int p = 0; p < B / 64; ++p)
-            for (int R = 0; R < 2; ++R)
+    const int r = ((blockIdx.x * blockDim.x + threadIdx.x) >> 6) * 32 + col;
+    const bool valid = r < rays;
+    const float* row = scores + (size_t)(valid ? r : rays - 1) * B;
+    TopList<NCAP> t;
+    t.init();
+    for (int b = 0; b < B / 4; b += 2)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int c = 64 * p + 32 * R + 8 * (i / 4) + (i % 4);
-                    t.push(row[c + 4 * g], c);
-                }
-        t.rebase(4 * g);
-        t.merge_partner();
-        int s[NCAP];
-        t.ascending(N, s);
-        if (g == 0 && valid)
-            for (int k = 0; k < N; ++k) out[(size_t)r * N + k] = pick<true>(s, k);
-    });
+        for (int j = 0; j < 4; ++j) t.push(row[4 * (b + g) + j], 4 * b + j);
+    t.rebase(4 * g);
+    t.merge_partner();
+    int s[NCAP];
+    t.ascending(N, s);
+    if (g == 0 && valid)
+        for (int k = 0; k < N; ++k) out[(size_t)r * N + k] = pick<true>(s, k);
+}
+
+// The selection of rows_kernel.h on given scores, over LANES lanes per ray.
+template <int NCAP, int LANES>
+__global__ void __launch_bounds__(256) topn_lanes_kernel(const float* scores, int32_t rays, int32_t N, int32_t B,
+                                                         int32_t* out) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    const int r = t / LANES, part = t % LANES;
+    const bool valid = r < rays;
+    const float* row = scores + (size_t)(valid ? r : rays - 1) * B;
+    int s[NCAP];
+    lanes_topn<NCAP, LANES>([&](int b) {
+        u32x4 v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = __float_as_uint(row[4 * b + j]);
+        return v;
+    }, part, B, N, s);
+    if (part == 0 && valid)
+        for (int k = 0; k < N; ++k) out[(size_t)r * N + k] = pick<true>(s, k);
 }
 
 }  // namespace
@@ -226,23 +239,30 @@ hipError_t launch_mfma_peak(int prec, int workgroups, int iters, uint32_t seed, 
     return hipGetLastError();
 }
 
-hipError_t launch_topn(bool bf16_layout, int ncap, const float* scores, int32_t rays, int32_t N,
-                       int32_t B, int32_t* out_idx, hipStream_t stream) {
-    const int cb = bf16_layout ? 2 : 1;
-    const int rays_per_block = 4 * 32 * cb;
-    const dim3 grid((rays + rays_per_block - 1) / rays_per_block);
-#define DN_TOPN(CB, NC) hipLaunchKernelGGL((topn_kernel<CB, NC>), grid, dim3(256), 0, stream, scores, rays, N, B, out_idx)
-    if (cb == 2) {
-        if (ncap == 4) DN_TOPN(2, 4);
-        else if (ncap == 8) DN_TOPN(2, 8);
-        else DN_TOPN(2, 16);
-    } else {
-        if (ncap == 4) DN_TOPN(1, 4);
-        else if (ncap == 8) DN_TOPN(1, 8);
-        else DN_TOPN(1, 16);
+hipError_t launch_topn(int prec, int tile_rays, int ncap, const float* scores, int32_t rays, int32_t N, int32_t B,
+                       int32_t* out_idx, hipStream_t stream) {
+    // rays per workgroup of 256 threads: 128 of two lanes, 32 of 8 or 16 of 16
+    const bool rows = prec == kF32 || tile_rays != rays_per_block(prec);
+    const int per = !rows ? 128 : tile_rays == 64 ? 32 : 16;
+    // only the main tile has a list of eight
+    const int cap = ncap == 8 && tile_rays != rays_per_block(prec) ? 16 : ncap;
+    using Kernel = void (*)(const float*, int32_t, int32_t, int32_t, int32_t*);
+    const Kernel kernel = !rows ? (cap == 4 ? topn_kernel<4> : cap == 8 ? topn_kernel<8> : topn_kernel<16>)
+                          : tile_rays == 64
+                              ? (cap == 4   ? topn_lanes_kernel<4, 8>
+                                 : cap == 8 ? topn_lanes_kernel<8, 8>
+                                            : topn_lanes_kernel<16, 8>)
+                              : (cap == 4 ? topn_lanes_kernel<4, 16> : topn_lanes_kernel<16, 16>);
+    constexpr int32_t kMost = 1 << 24;   // rays of a launch: thread numbers stay below 2^31
+    for (int32_t left = rays; left > 0; left -= kMost) {
+        const int32_t n = left < kMost ? left : kMost;
+        hipLaunchKernelGGL(kernel, dim3((n + per - 1) / per), dim3(256), 0, stream, scores, n, N, B, out_idx);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        scores += (size_t)n * B;
+        out_idx += (size_t)n * N;
     }
-#undef DN_TOPN
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace donerf

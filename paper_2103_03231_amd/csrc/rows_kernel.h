@@ -179,6 +179,21 @@ __device__ __forceinline__ void merge_lanes(TopList<NCAP>& top) {
     });
 }
 
+// The N best of a ray's B classes in ascending order, lane part of LANES taking
+// the blocks part, part + LANES, ... of four classes; block(b): their scores.
+template <int NCAP, int LANES, class Block>
+__device__ __forceinline__ void lanes_topn(Block&& block, int part, int B, int N, int (&sel)[NCAP]) {
+    TopList<NCAP> top;
+    top.init();
+    for (int b = part; b < B / 4; b += LANES) {
+        const u32x4 s = block(b);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) top.push(__uint_as_float(s[j]), 4 * b + j);
+    }
+    merge_lanes<NCAP, LANES>(top);
+    top.ascending(N, sel);
+}
+
 // ------------------------------------------------------------------ the kernel body
 
 // PR: network precision.  CB: 32-ray column blocks.  NCAP: capacity of the
@@ -475,16 +490,8 @@ struct RowsRender {
     static constexpr int LPR = kRowThreads / R;   // lanes per ray: 16 or 8
     __device__ __forceinline__ void select_topn() const {
         const int ray = wave * (64 / LPR) + lane / LPR, part = lane % LPR;
-        TopList<NCAP> top;
-        top.init();
-        for (int b = part; b < a.B / 4; b += LPR) {
-            const u32x4 s = sh.pool[b * kScoreRow + ray];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) top.push(__uint_as_float(s[j]), 4 * b + j);
-        }
-        merge_lanes<NCAP, LPR>(top);
         int sel[NCAP];
-        top.ascending(a.N, sel);
+        lanes_topn<NCAP, LPR>([&](int b) { return sh.pool[b * kScoreRow + ray]; }, part, a.B, a.N, sel);
         if (part == 0) {
 #pragma unroll
             for (int k = 0; k < NCAP; ++k)

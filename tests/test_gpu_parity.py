@@ -182,6 +182,27 @@ def test_topn_bit_exact(precision, B):
     r.close()
 
 
+@pytest.mark.parametrize("precision,tile", [("fp32", 32), ("fp32", 64), ("bf16", 32), ("bf16", 64), ("bf16", 256),
+                                            ("fp8", 32), ("fp8", 64), ("fp8", 128)])
+@pytest.mark.parametrize("B", [64, 128, 192, 256])
+def test_topn_bit_exact_on_every_tile(precision, tile, B):
+    """The selection of every kernel (a ray's classes over 2, 8 or 16 lanes, lists
+    of 4, 8 and 16; with B = 64 and N = 16 a lane's list is not filled by its own
+    classes): as many rays as the planner renders on that tile."""
+    r, _ = renderer(precision, n_bins=B, n_max=16)
+    for N in (1, 4, 5, 8, 9, 16):
+        rays = next(n for n in (1, 77, 1009, 3001, 9001, 13001, 20011, 30011, 70001, 100003)
+                    if b.donerf_debug_plan(r.cfg, 1, 1, n, N)["tile_rays"] == tile)
+        for mode in ("normal", "ties", "const", "special"):
+            lg = inputs.random_logits(rays, B, seed=B + N, mode=mode)
+            dev = torch.from_numpy(lg).cuda()
+            out = torch.empty((rays, N), dtype=torch.int32, device="cuda")
+            b.donerf_debug_topn(r.h, dev.data_ptr(), rays, N, out.data_ptr())
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy(), O.topn(lg, N)), (rays, N, mode)
+    r.close()
+
+
 def test_topn_million_rows():
     r, _ = renderer("bf16", n_bins=128, n_max=4)
     lg = inputs.random_logits(1_000_000, 128, seed=99)
