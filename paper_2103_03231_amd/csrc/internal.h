@@ -89,17 +89,15 @@ inline int tile_threads(int prec, int tile_rays) {
 // kernel's, or rows_kernel.h's smaller tiles'.
 hipError_t launch_render(int prec, int ncap, int place, int din, const RenderArgs& a, uint32_t n_split_tiles,
                          hipStream_t stream);
-// The variants of one precision and placement (render_*.hip).
+// The main kernels of bf16 and fp8 networks by placement (render_*.hip).
 hipError_t launch_render_bf16_topn(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
 hipError_t launch_render_bf16_cdf(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
-hipError_t launch_render_fp32_topn(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
-hipError_t launch_render_fp32_cdf(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
+hipError_t launch_render_bf16_cdf_wide(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
 hipError_t launch_render_fp8_topn(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
 hipError_t launch_render_fp8_cdf(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
-hipError_t launch_render_bf16_cdf_wide(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
-hipError_t launch_render_fp32_cdf_wide(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
 hipError_t launch_render_fp8_cdf_wide(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
-// rows_kernel.h's tiles: 32 rays, or 64 for bf16 and fp8 (render_rows_*.hip).
+// rows_kernel.h's tiles of 32 and 64 rays, for fp32 networks all there are
+// (render_rows_*.hip); any other tile is hipErrorInvalidValue.
 hipError_t launch_rows_bf16(int cdf, int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
 hipError_t launch_rows_fp8(int cdf, int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);
 hipError_t launch_rows_fp32(int cdf, int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream);

@@ -94,24 +94,18 @@ __global__ void __launch_bounds__(256) topn_lanes_kernel(const float* scores, in
 hipError_t launch_render(int prec, int ncap, int place, int din, const RenderArgs& a, uint32_t n_split_tiles,
                          hipStream_t stream) {
     const dim3 grid(a.n_full + n_split_tiles * (uint32_t)a.split);
-    if (a.tile_rays != rays_per_block(prec)) {
-        const int cdf = place != kPlaceTopN;
-        return prec == kFP8    ? launch_rows_fp8(cdf, ncap, din, a, grid, stream)
-               : prec == kBF16 ? launch_rows_bf16(cdf, ncap, din, a, grid, stream)
-                               : launch_rows_fp32(cdf, ncap, din, a, grid, stream);
-    }
-    if (place == kPlaceCdfWide)
-        return prec == kFP8    ? launch_render_fp8_cdf_wide(ncap, din, a, grid, stream)
-               : prec == kBF16 ? launch_render_bf16_cdf_wide(ncap, din, a, grid, stream)
-                               : launch_render_fp32_cdf_wide(ncap, din, a, grid, stream);
+    const int cdf = place != kPlaceTopN;
+    if (prec == kF32) return launch_rows_fp32(cdf, ncap, din, a, grid, stream);
+    if (a.tile_rays != rays_per_block(prec))
+        return prec == kFP8 ? launch_rows_fp8(cdf, ncap, din, a, grid, stream)
+                            : launch_rows_bf16(cdf, ncap, din, a, grid, stream);
     if (prec == kFP8)
-        return place == kPlaceCdf ? launch_render_fp8_cdf(ncap, din, a, grid, stream)
-                                  : launch_render_fp8_topn(ncap, din, a, grid, stream);
-    if (prec == kBF16)
-        return place == kPlaceCdf ? launch_render_bf16_cdf(ncap, din, a, grid, stream)
-                                  : launch_render_bf16_topn(ncap, din, a, grid, stream);
-    return place == kPlaceCdf ? launch_render_fp32_cdf(ncap, din, a, grid, stream)
-                              : launch_render_fp32_topn(ncap, din, a, grid, stream);
+        return place == kPlaceTopN  ? launch_render_fp8_topn(ncap, din, a, grid, stream)
+               : place == kPlaceCdf ? launch_render_fp8_cdf(ncap, din, a, grid, stream)
+                                    : launch_render_fp8_cdf_wide(ncap, din, a, grid, stream);
+    return place == kPlaceTopN  ? launch_render_bf16_topn(ncap, din, a, grid, stream)
+           : place == kPlaceCdf ? launch_render_bf16_cdf(ncap, din, a, grid, stream)
+                                : launch_render_bf16_cdf_wide(ncap, din, a, grid, stream);
 }
 
 // ------------------------------------------------------------------ static scratch

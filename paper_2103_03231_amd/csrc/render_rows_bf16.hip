@@ -6,12 +6,9 @@
 namespace donerf {
 
 hipError_t launch_rows_bf16(int cdf, int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream) {
-    if (a.tile_rays == 32)
-        return cdf ? launch_rows<kBF16, 1, true>(ncap, din, a, grid, stream)
-                   : launch_rows<kBF16, 1, false>(ncap, din, a, grid, stream);
-    if (a.tile_rays != 64) return hipErrorInvalidValue;   // no such tile
-    return cdf ? launch_rows<kBF16, 2, true>(ncap, din, a, grid, stream)
-               : launch_rows<kBF16, 2, false>(ncap, din, a, grid, stream);
+    return a.tile_rays == 32   ? launch_rows<kBF16, 1>(cdf, ncap, din, a, grid, stream)
+           : a.tile_rays == 64 ? launch_rows<kBF16, 2>(cdf, ncap, din, a, grid, stream)
+                               : hipErrorInvalidValue;   // no such tile
 }
 
 }  // namespace donerf

@@ -601,11 +601,10 @@ struct RowsFp8 {
     }
 };
 
-// The main kernel of fp8 networks, with render_kernel's parameters.
-template <int PR, int CB, int NW, int OCC, int NCAP, int PLACE, int DIN>
-__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
+// The main kernel of fp8 networks.
+template <int NCAP, int PLACE, int DIN>
+__global__ void __launch_bounds__(64 * kF8Waves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 fp8_render_kernel(const RenderArgs a) {
-    static_assert(PR == kFP8 && CB == kF8CB && NW == kF8Waves && OCC == 2, "launch shape");
     using K = RowsFp8<NCAP, PLACE, DIN>;
     __shared__ typename K::Shared sh;
     K k{a, sh};
@@ -615,12 +614,9 @@ fp8_render_kernel(const RenderArgs a) {
 template <int PL, int DIN>
 hipError_t launch_fp8_variant(int ncap, const RenderArgs& a, dim3 grid, hipStream_t stream) {
     const dim3 block(64 * kF8Waves);
-    if (ncap == 4)
-        hipLaunchKernelGGL((fp8_render_kernel<kFP8, kF8CB, kF8Waves, 2, 4, PL, DIN>), grid, block, 0, stream, a);
-    else if (ncap == 8)
-        hipLaunchKernelGGL((fp8_render_kernel<kFP8, kF8CB, kF8Waves, 2, 8, PL, DIN>), grid, block, 0, stream, a);
-    else
-        hipLaunchKernelGGL((fp8_render_kernel<kFP8, kF8CB, kF8Waves, 2, 16, PL, DIN>), grid, block, 0, stream, a);
+    if (ncap == 4) hipLaunchKernelGGL((fp8_render_kernel<4, PL, DIN>), grid, block, 0, stream, a);
+    else if (ncap == 8) hipLaunchKernelGGL((fp8_render_kernel<8, PL, DIN>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((fp8_render_kernel<16, PL, DIN>), grid, block, 0, stream, a);
     return hipGetLastError();
 }
 

@@ -923,8 +923,10 @@ struct RowsRender {
     }
 };
 
-// Tiles of 32 CB rays for calls too small to fill the chip with the tiles of
-// the precision's main kernel.
+// Tiles of 32 CB rays: the main kernel of fp32 networks (64 rays: with 96 the
+// three planes leave no LDS for the tables, with 32 every weight feeds half the
+// work), and the tiles of calls too small to fill the chip with the main
+// kernel's.
 template <int PR, int CB, int NCAP, bool CDF, int DIN>
 __global__ void __launch_bounds__(kRowThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 render_rows(const RenderArgs a) {
@@ -934,49 +936,33 @@ render_rows(const RenderArgs a) {
     k.run();
 }
 
-// The main kernel of fp32 networks (64 rays: with 96 the three planes leave
-// no LDS for the tables, with 32 every weight feeds half the work), with render_kernel's parameters.
-template <int PR, int CB, int NW, int OCC, int NCAP, int PLACE, int DIN>
-__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
-rows_render_kernel(const RenderArgs a) {
-    static_assert(NW == kRowWaves, "waves per workgroup");
-    using K = RowsRender<PR, CB, NCAP, PLACE != kPlaceTopN, DIN>;
-    __shared__ typename K::Shared sh;
-    K k{a, sh};
-    k.run();
-}
-
+// A list of 8 pays on the fp32 tiles of 64 rays only: 4 or 16 otherwise.
 template <int PR, int CB, bool CDF, int DIN>
 hipError_t launch_rows_variant(int ncap, const RenderArgs& a, dim3 grid, hipStream_t stream) {
-    if (CDF || ncap > 4)
-        hipLaunchKernelGGL((render_rows<PR, CB, 16, CDF, DIN>), grid, dim3(kRowThreads), 0, stream, a);
-    else
-        hipLaunchKernelGGL((render_rows<PR, CB, CDF ? 16 : 4, CDF, DIN>), grid, dim3(kRowThreads), 0, stream, a);
-    return hipGetLastError();
-}
-
-template <int PR, int CB, bool CDF>
-hipError_t launch_rows(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream) {
-    return din == kDinPositions ? launch_rows_variant<PR, CB, CDF, kDinPositions>(ncap, a, grid, stream)
-                                : launch_rows_variant<PR, CB, CDF, kDinEncoded>(ncap, a, grid, stream);
-}
-
-template <int PR, int CB, int PL, int DIN>
-hipError_t launch_rows_main_variant(int ncap, const RenderArgs& a, dim3 grid, hipStream_t stream) {
     const dim3 block(kRowThreads);
-    if (ncap == 4)
-        hipLaunchKernelGGL((rows_render_kernel<PR, CB, kRowWaves, 2, 4, PL, DIN>), grid, block, 0, stream, a);
-    else if (ncap == 8)
-        hipLaunchKernelGGL((rows_render_kernel<PR, CB, kRowWaves, 2, 8, PL, DIN>), grid, block, 0, stream, a);
-    else
-        hipLaunchKernelGGL((rows_render_kernel<PR, CB, kRowWaves, 2, 16, PL, DIN>), grid, block, 0, stream, a);
+    if constexpr (CDF) {
+        hipLaunchKernelGGL((render_rows<PR, CB, 16, true, DIN>), grid, block, 0, stream, a);
+    } else if (ncap == 4) {
+        hipLaunchKernelGGL((render_rows<PR, CB, 4, false, DIN>), grid, block, 0, stream, a);
+    } else {
+        if constexpr (PR == kF32 && CB == kF32CB) {
+            if (ncap == 8) {
+                hipLaunchKernelGGL((render_rows<PR, CB, 8, false, DIN>), grid, block, 0, stream, a);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((render_rows<PR, CB, 16, false, DIN>), grid, block, 0, stream, a);
+    }
     return hipGetLastError();
 }
 
-template <int PR, int CB, int PL>
-hipError_t launch_rows_main(int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream) {
-    return din == kDinPositions ? launch_rows_main_variant<PR, CB, PL, kDinPositions>(ncap, a, grid, stream)
-                                : launch_rows_main_variant<PR, CB, PL, kDinEncoded>(ncap, a, grid, stream);
+template <int PR, int CB>
+hipError_t launch_rows(int cdf, int ncap, int din, const RenderArgs& a, dim3 grid, hipStream_t stream) {
+    if (din == kDinPositions)
+        return cdf ? launch_rows_variant<PR, CB, true, kDinPositions>(ncap, a, grid, stream)
+                   : launch_rows_variant<PR, CB, false, kDinPositions>(ncap, a, grid, stream);
+    return cdf ? launch_rows_variant<PR, CB, true, kDinEncoded>(ncap, a, grid, stream)
+               : launch_rows_variant<PR, CB, false, kDinEncoded>(ncap, a, grid, stream);
 }
 
 }  // namespace

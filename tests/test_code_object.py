@@ -1,7 +1,7 @@
 """Resource use of the built gfx950 kernels, read from the library's code
 object without a GPU: every render kernel fits one workgroup's LDS, and the
-top-N render kernels and those of fp8 networks read neither the dispatch packet
-nor scratch memory.
+top-N render kernels, and all those of fp32 and fp8 networks and of small tiles,
+read neither the dispatch packet nor scratch memory.
 
 A kernel that indexes a small per-lane array at a computed index gets that
 array moved into a per-thread LDS block, whose address is built from the
@@ -88,43 +88,51 @@ def kernels():
     return out
 
 
-# render_kernel<PR, CB, NW, OCC, NCAP, PLACE, DIN>, mangled
-RENDER = re.compile(r"render_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)EEEv")
+# mangled names: render_kernel<PR, CB, NW, OCC, NCAP, PLACE, DIN> (bf16),
+# fp8_render_kernel<NCAP, PLACE, DIN>, render_rows<PR, CB, NCAP, CDF, DIN>
+BF16 = re.compile(r"\d13render_kernelILi1ELi1ELi8ELi2ELi(\d+)ELi(\d)ELi(\d)EEEv")
+FP8 = re.compile(r"17fp8_render_kernelILi(\d+)ELi(\d)ELi(\d)EEEv")
+ROWS = re.compile(r"11render_rowsILi(\d)ELi(\d)ELi(\d+)ELb(\d)ELi(\d)EEEv")
 
 
-def _render(kernels):
-    out = []
+def _match(kernels, pattern):
+    out = {}
     for name, d in kernels.items():
-        m = RENDER.search(name)
+        m = pattern.search(name)
         if m:
-            out.append((tuple(int(x) for x in m.groups()), d))
+            out[tuple(int(x) for x in m.groups())] = d
     return out
 
 
-def test_every_precision_and_placement_is_built(kernels):
-    got = {(pr, place) for (pr, _, _, _, _, place, _), _ in _render(kernels)}
-    assert got == {(pr, place) for pr in (0, 1, 2) for place in (0, 1, 2)}
+MAIN = {(ncap, place, din) for ncap in (4, 8, 16) for place in (0, 1, 2) for din in (0, 1)}
+# precision, 32-ray blocks of a tile: top-N lists of 4 and 16 (fp32 tiles of 64
+# rays: and 8), inverse CDF with room for 16 samples
+SMALL = {(pr, cb, ncap, cdf, din) for pr, cb in ((0, 1), (0, 2), (1, 1), (1, 2), (2, 1), (2, 2))
+         for ncap, cdf in ((4, 0), (16, 0), (16, 1)) + (((8, 0),) if (pr, cb) == (0, 2) else ()) for din in (0, 1)}
+
+
+def test_every_render_kernel_is_built(kernels):
+    assert set(_match(kernels, BF16)) == MAIN
+    assert set(_match(kernels, FP8)) == MAIN
+    assert set(_match(kernels, ROWS)) == SMALL
+    named = [n for n in kernels if "render" in n]
+    assert len(named) == 2 * len(MAIN) + len(SMALL), sorted(named)
 
 
 def test_render_kernels_fit_the_lds(kernels):
-    for params, (lds, _, _) in _render(kernels):
-        assert 0 < lds <= LDS_PER_CU, (params, lds)
+    for pattern, workgroups in ((BF16, 1), (FP8, 2), (ROWS, 1)):
+        for params, (lds, _, _) in _match(kernels, pattern).items():
+            assert 0 < lds <= LDS_PER_CU // workgroups, (params, lds)
 
 
-def test_topn_kernels_read_no_dispatch_packet_and_no_scratch(kernels):
-    topn = [(p, d) for p, d in _render(kernels) if p[5] == 0]
-    assert len(topn) == 3 * 3 * 2   # precisions x sample capacities x depth inputs
-    for params, (lds, scratch, dispatch) in topn:
+def test_kernels_read_no_dispatch_packet_and_no_scratch(kernels):
+    """Every top-N kernel of bf16 networks, and every kernel of the others and of
+    the small tiles: inverse CDF too, where a ray's samples are in LDS (small
+    tiles) or stay in registers through a kernel that fills most of them (fp8)."""
+    checked = {("bf16", *p): d for p, d in _match(kernels, BF16).items() if p[1] == 0}
+    checked.update({("fp8", *p): d for p, d in _match(kernels, FP8).items()})
+    checked.update({("rows", *p): d for p, d in _match(kernels, ROWS).items()})
+    assert len(checked) == 6 + len(MAIN) + len(SMALL)
+    for params, (_, scratch, dispatch) in checked.items():
         assert not dispatch, ("reads the dispatch packet", params)
         assert scratch == 0, ("spills to scratch", params, scratch)
-
-
-def test_fp8_kernels_read_no_dispatch_packet_and_no_scratch(kernels):
-    """Inverse-CDF placement included: a ray's depths and slice ends stay in
-    registers through a kernel that fills most of them."""
-    fp8 = [(p, d) for p, d in _render(kernels) if p[0] == 2]
-    assert len(fp8) == 3 * 3 * 2   # placements x sample capacities x depth inputs
-    for params, (lds, scratch, dispatch) in fp8:
-        assert scratch == 0, ("spills to scratch", params, scratch)
-        assert not dispatch, ("reads the dispatch packet", params)
-        assert lds <= LDS_PER_CU // 2, ("two workgroups share a CU", params, lds)
