@@ -23,7 +23,8 @@ struct donerf_handle {
     void* d_frags;       // device: depth stream then shading stream (fp32: layout.h rows32_layer_frags)
     float* bias;         // device
     float* bins;         // device: centres[B], widths[B], bounds[B + 1]
-    int n_d_chunks, n_s_chunks, bias_len;
+    int n_d_chunks, n_s_chunks;   // bf16 networks: chunks of the two streams
+    int bias_len;
     size_t s_off;        // bytes of the depth stream, where the shading stream begins
     int n_cu;            // compute units: workgroups of one full round
     float* partial;      // device: split-tail parts, n_cu * 256 rays * 5 floats
@@ -598,7 +599,7 @@ int donerf_create(const donerf_cfg* cfg, const float* weights, size_t n_weights,
         } else {
             pack_layer(fp, prec, kind, kind == kHiddenL ? l % 8 - 1 : -1, B, weights + off, s, frags);
         }
-        (l < 8 ? n_d_chunks : n_s_chunks) += layer_chunks(prec, kind, B);
+        if (prec == kBF16) (l < 8 ? n_d_chunks : n_s_chunks) += layer_chunks(prec, kind, B);
         if (l == 7 && wide_cdf(*cfg) && prec == kBF16) {
             pack_layer(fp, prec, kind, -1, B, weights + off, s, frags);
             n_d_chunks += layer_chunks(prec, kind, B);

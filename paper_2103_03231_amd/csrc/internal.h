@@ -13,8 +13,8 @@ constexpr int kMaxSamples = 16;   // samples per ray (include/donerf.h DONERF_MA
 
 // Everything one render launch needs, passed by value as the kernel argument.
 struct RenderArgs {
-    const uint4* d_frags;   // depth network fragments, chunk-padded per layer
-    const uint4* s_frags;   // shading network fragments, chunk-padded per layer
+    const uint4* d_frags;   // depth network fragments (bf16 and fp8 networks: chunk-padded per layer)
+    const uint4* s_frags;   // shading network fragments
     const float* bias;      // all biases (layout.h bias_len); the depth head's last
     const float* bins;      // centres[B] then widths[B]
     float* out_rgb;         // rays x 3
@@ -22,7 +22,7 @@ struct RenderArgs {
     int32_t* out_bins;      // rays x N, or null
     float* out_scores;      // rays x B, or null
     float* out_samples;     // rays x N x (depth, width), or null
-    int32_t n_d_chunks;
+    int32_t n_d_chunks;     // chunks of the two streams, for the kernel that copies them (bf16)
     int32_t n_s_chunks;
     int32_t bias_len;       // floats in bias
     int32_t H, W, n_poses, N, B;

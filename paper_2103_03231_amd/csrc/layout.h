@@ -7,7 +7,8 @@
 //   bf16: v_mfma_f32_32x32x16_bf16, 32 rows x 16 K; lane l holds row l%32 and
 //         K slots 8*(l/32) + e, e = 0..7 (16 bytes)
 //   fp32: four v_mfma_f32_32x32x2_f32, 32 rows x 8 K; lane l holds row l%32,
-//         sub-step e = 0..3 reads K slot 2*e + l/32 (16 bytes)
+//         sub-step e = 0..3 reads K slot 2*e + l/32 (16 bytes); the folded
+//         positions layer only (fp32 networks: rows32_* below)
 //   fp8:  v_mfma_scale_f32_32x32x64_f8f6f4 on E4M3, 32 rows x 64 K; lane l
 //         holds row l%32 and 32 K elements (32 bytes).  A and B place K the
 //         same way, so element e of lane group g of A multiplies element e of
@@ -65,13 +66,11 @@ DN_HD constexpr int ksteps(int p, int kpad) { return kpad / kper(p); }
 
 // Hidden unit (logical row of the previous layer) that feeds K step ks,
 // lane group g, element e when the previous layer's accumulators are chained.
-// bf16 / fp32: a 32-row block feeds 2 / 4 K steps.  fp8: a K step takes the
-// 16 registers of two consecutive blocks, elements 0-15 from the first.
+// bf16: a 32-row block feeds 2 K steps.  fp8: a K step takes the 16 registers of
+// two consecutive blocks, elements 0-15 from the first.
 DN_HD constexpr int chained_row(int p, int ks, int g, int e) {
     return p == kFP8 ? 32 * (2 * ks + e / 16) + 8 * ((e % 16) / 4) + 4 * g + e % 4
-                     : 32 * (ks / (16 / elems(p))) +
-                           8 * (((ks % (16 / elems(p))) * elems(p) + e) / 4) + 4 * g +
-                           (((ks % (16 / elems(p))) * elems(p) + e) % 4);
+                     : 32 * (ks / 2) + 8 * (((ks % 2) * 8 + e) / 4) + 4 * g + e % 4;
 }
 
 // bf16 networks run their six hidden layers on v_mfma_f32_16x16x32_bf16:
@@ -194,10 +193,10 @@ DN_HD constexpr int layer_frags(int net, int kind, int n_bins) {
 // to an even number of chunks, so that each starts in slot 0 of the two-slot
 // LDS stream and the slot of every chunk is known at compile time.  The
 // shading network's first layer and head are not: a sample's chunks add up to
-// an even number (bf16 1 + 24 + 1, fp8 1 + 12 + 1), so every
-// sample still starts in slot 0 and its layers' slots stay compile-time
-// constants, and the two padding chunks per sample it saves are two barriers
-// and two copies (0.45 % of the bf16 and 1.1 % of the fp8 step).
+// an even number (1 + 24 + 1), so every sample still starts in slot 0 and its
+// layers' slots stay compile-time constants, and the two padding chunks per
+// sample it saves are two barriers and two copies (0.45 % of the step).  The fp8
+// stream has the same padding, though its kernels read fragments by address.
 DN_HD constexpr bool layer_even_padded(int kind) { return !(kind == kSFirst || kind == kSHead); }
 DN_HD constexpr int layer_chunks(int net, int kind, int n_bins) {
     return layer_even_padded(kind)

@@ -762,37 +762,25 @@ __device__ __forceinline__ void warp(const RenderArgs& a, const float (&x)[3], f
 }
 
 // Encoding slots: T frequency pairs 2t + g (t < T) of v, written as
-// [sin x, sin y, sin z, cos x, cos y, cos z] per frequency.  The scale 2^k is
-// exact in fp32.  EXACT (fp32 networks): sincospif at every frequency, which
-// avoids multiplying by a rounded pi.  Otherwise (bf16 features) the
-// hardware sine and cosine, which take revolutions: y = v 2^(k-1) and its
-// distance to the nearest integer r = y - rint(y) are exact, so sin(pi v 2^k)
-// = sin(2 pi r) with r in [-1/2, 1/2], the range the hardware is accurate on.
-// Measured against fp64 over that range and the encodings' arguments (up to
-// about 280 revolutions before reduction): at most 1.3e-7 absolute error,
-// far below the bf16 rounding the features then undergo.
-#ifndef DONERF_PE_EXACT
-#define DONERF_PE_EXACT 0
-#endif
-template <int T, bool EXACT>
+// [sin x, sin y, sin z, cos x, cos y, cos z] per frequency, for bf16 features
+// (fp32 networks: rows_kernel.h fourier_pair).  The hardware sine and cosine take
+// revolutions: y = v 2^(k-1) and its distance to the nearest integer r = y -
+// rint(y) are exact, so sin(pi v 2^k) = sin(2 pi r) with r in [-1/2, 1/2], the
+// range the hardware is accurate on.  Measured against fp64 over that range and
+// the encodings' arguments (up to about 280 revolutions before reduction): at
+// most 1.3e-7 absolute error, far below the bf16 rounding the features then
+// undergo.
+template <int T>
 __device__ __forceinline__ void fourier(const float (&v)[3], int g, float* f) {
     const float gs = g ? 2.0f : 1.0f;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            float s, co;
-            if (EXACT || DONERF_PE_EXACT) {
-                const float sc = (float)(1u << (2 * t)) * gs;
-                sincospif(v[c] * sc, &s, &co);
-            } else {
-                const float y = v[c] * ((float)(1u << (2 * t)) * 0.5f * gs);
-                const float r = y - __builtin_rintf(y);
-                s = __builtin_amdgcn_sinf(r);
-                co = __builtin_amdgcn_cosf(r);
-            }
-            f[6 * t + c] = s;
-            f[6 * t + 3 + c] = co;
+            const float y = v[c] * ((float)(1u << (2 * t)) * 0.5f * gs);
+            const float r = y - __builtin_rintf(y);
+            f[6 * t + c] = __builtin_amdgcn_sinf(r);
+            f[6 * t + 3 + c] = __builtin_amdgcn_cosf(r);
         }
     }
 }
@@ -916,8 +904,8 @@ render_kernel(const RenderArgs a) {
         v[2] = (ou[2] - a.cz) / a.dmax;
         float f[kDSlots];
         if constexpr (DIN == kDinEncoded) {
-            fourier<5, false>(v, g, f);
-            fourier<2, false>(ray[cb].r, g, f + 30);
+            fourier<5>(v, g, f);
+            fourier<2>(ray[cb].r, g, f + 30);
             f[42] = g ? ray[cb].r[0] : v[0];
             f[43] = g ? ray[cb].r[1] : v[1];
             f[44] = g ? ray[cb].r[2] : v[2];
@@ -940,7 +928,7 @@ render_kernel(const RenderArgs a) {
             }
             din[0][cb] = Prec<kF32>::pack(q);
             din[1][cb] = Prec<kF32>::pack(q + 4);
-            fourier<2, false>(ray[cb].r, g, f + 30);
+            fourier<2>(ray[cb].r, g, f + 30);
         }
         // the direction skip of the last shading layer: the same direction
         // encoding plus the identity
@@ -1296,7 +1284,7 @@ render_kernel(const RenderArgs a) {
             for (int c = 0; c < 3; ++c) x[c] = ray[cb].o[c] + tk[cb] * ray[cb].r[c];
             warp(a, x, w);
             float f[kSSlots];
-            fourier<5, false>(w, g, f);
+            fourier<5>(w, g, f);
             f[30] = g ? w[2] : w[0];
             f[31] = g ? 0.0f : w[1];
 #pragma unroll

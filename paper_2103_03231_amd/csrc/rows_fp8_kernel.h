@@ -369,8 +369,8 @@ struct RowsFp8 {
             v[2] = (ou[2] - a.cz) / a.dmax;
             float f[kDSlots];
             if constexpr (DIN == kDinEncoded) {
-                fourier<5, false>(v, g, f);
-                fourier<2, false>(ray.r, g, f + 30);
+                fourier<5>(v, g, f);
+                fourier<2>(ray.r, g, f + 30);
                 f[42] = g ? ray.r[0] : v[0];
                 f[43] = g ? ray.r[1] : v[1];
                 f[44] = g ? ray.r[2] : v[2];
@@ -384,7 +384,7 @@ struct RowsFp8 {
                                     g ? uc[1] : uc[0],       g ? 0.0f : uc[2],    0.0f, 0.0f, 0.0f};
                 sh.pool[g * R + rl()] = Prec<kF32>::pack(q);
                 sh.pool[(2 + g) * R + rl()] = Prec<kF32>::pack(q + 4);
-                fourier<2, false>(ray.r, g, f + 30);
+                fourier<2>(ray.r, g, f + 30);
             }
             float fs[kSkipSlots];
 #pragma unroll
@@ -540,7 +540,7 @@ struct RowsFp8 {
                 for (int i = 0; i < 3; ++i) x[i] = ray.o[i] + tk * ray.r[i];
                 warp(a, x, w);
                 float f[kSSlots];
-                fourier<5, false>(w, g, f);
+                fourier<5>(w, g, f);
                 f[30] = g ? w[2] : w[0];
                 f[31] = g ? 0.0f : w[1];
 #pragma unroll

@@ -131,7 +131,8 @@ __device__ __forceinline__ float fourier_slot(const float (&v)[3], int g) {
     return S % 6 < 3 ? __builtin_amdgcn_sinf(r) : __builtin_amdgcn_cosf(r);
 }
 
-// Argument q of an encoding by pairs (layout.h pair_feature).
+// Argument q of an encoding by pairs (layout.h pair_feature), for fp32 features:
+// sincospif avoids multiplying by a rounded pi.
 __device__ __forceinline__ void fourier_pair(const float (&v)[3], int q, float& sn, float& co) {
     const int f = q / 3, c = q - 3 * f;
     sincospif((c == 0 ? v[0] : c == 1 ? v[1] : v[2]) * (float)(1u << f), &sn, &co);
