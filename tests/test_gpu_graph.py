@@ -14,9 +14,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("precision,poses,H,W,N", [
-    ("bf16", [0, 3], 96, 80, 4),          # few tiles: the split tail and its combine kernel
+    ("bf16", [0, 3], 96, 80, 4),          # tiles of 64 rays
+    ("bf16", [0, 1, 2], 150, 151, 4),     # the split tail of the main kernel's tiles and its combine kernel
     ("bf16", [0, 1, 2, 3, 4], 400, 400, 4),
-    ("fp8", [1], 61, 47, 8),
+    ("fp8", [1], 61, 47, 8),              # tiles of 64 rays, all split
 ])
 def test_render_replays_from_a_graph(precision, poses, H, W, N):
     prec = {"bf16": b.BF16, "fp8": b.FP8}[precision]

@@ -241,7 +241,7 @@ def test_bf16_small_frames_against_bf16_oracle():
     (8, 256, 16, 24, 1),
     (16, 256, 12, 20, 1),
     (4, 192, 3, 5, 35),       # more poses than one launch holds
-    (1, 128, 1, 1, 1),        # a single ray: one tile of 255 idle columns
+    (1, 128, 1, 1, 1),        # a single ray: one tile of 31 idle columns
     (4, 128, 1, 1, 1),        # a single ray split four ways by samples, then combined
 ])
 def test_variants(precision, N, B, H, W, P):
@@ -304,9 +304,9 @@ def test_deterministic_and_plain_render_matches_debug():
                                                   ("bf16", "cdf", 256, 4)])
 def test_batching_invariance(precision, select, B, N):
     """A ray's result does not depend on the launch it is in.  Three views of
-    150 x 150 rendered together fill more than one round of 256 tiles and
-    split only the last 8 tiles N ways; each view alone is 88 tiles, all
-    split 2 ways by samples.  Every ray so sits in another tile, another
+    150 x 150 rendered together fill more than one round of tiles (256 of 256
+    rays; fp8: 512 of 128) and split only the last 8 (16) N ways; each view alone
+    is 88 (176) tiles, all split 2 ways by samples.  Every ray so sits in another tile, another
     workgroup and mostly another split.  The depth network and the selection
     (scores, classes, sample depths and widths) are bit-identical; the colour
     and depth may differ only by the order in which a split ray's parts are
@@ -315,6 +315,9 @@ def test_batching_invariance(precision, select, B, N):
     r, _ = renderer(precision, n_bins=B, n_max=N, select=sel, seed=2)
     poses = inputs.make_poses([7, 8, 9])
     H, W = 150, 150
+    one, three = (b.donerf_debug_plan(r.cfg, P, H, W, N) for P in (1, 3))
+    assert one["n_full"] == 0 and one["split"] == 2, one
+    assert three["n_full"] > 0 and three["split"] == N and three["tile_rays"] == one["tile_rays"], three
     together = gpu_render(r, poses, H, W, N)
     for i in range(len(poses)):
         alone = gpu_render(r, poses[i:i + 1], H, W, N)
@@ -531,15 +534,19 @@ def test_stereo_n16_b256_bf16_sampled():
     _sampled("stereo1440x1600_n16_b256_bf16", 800)
 
 
-def test_split_tail_matches_whole_tiles():
-    """The same rays rendered whole (in full rounds of one workgroup per CU)
-    and split by samples (a launch's partial last round) agree to fp32
-    rounding of the compositing."""
+@pytest.mark.parametrize("H,W,tile", [(64, 64, 64), (128, 128, 256)])
+def test_split_tail_matches_whole_tiles(H, W, tile):
+    """The same rays rendered whole (in full rounds of one workgroup per CU, on
+    tiles of 256 rays) and split by samples (a launch's partial last round, on
+    tiles of either size) agree to fp32 rounding of the compositing."""
     r, _ = renderer("bf16", n_max=8)
     pose = inputs.make_poses([6])
-    H, W, N = 64, 64, 8
-    alone = gpu_render(r, pose, H, W, N)                          # 16 tiles: split 8 ways
-    batch = gpu_render(r, np.repeat(pose, 32, axis=0), H, W, N)  # 512 tiles: two whole rounds
+    N = 8
+    small, whole = (b.donerf_debug_plan(r.cfg, P, H, W, N) for P in (1, 32))
+    assert (small["tile_rays"], small["n_full"]) == (tile, 0) and small["split"] > 1, small
+    assert (whole["tile_rays"], whole["split"]) == (256, 1), whole
+    alone = gpu_render(r, pose, H, W, N)
+    batch = gpu_render(r, np.repeat(pose, 32, axis=0), H, W, N)
     for idx in (0, 31):
         other = {k: v.reshape(32, -1)[idx] for k, v in batch.items()}
         for k in ("bins", "scores"):

@@ -30,6 +30,8 @@ PREC = {"fp32": b.FP32, "bf16": b.BF16, "fp8": b.FP8}
     ("fp8", "topn", "encoded", 64, 16),
     ("fp8", "cdf", "positions", 128, 2),
     ("fp8", "cdf", "encoded", 192, 6),
+    ("fp8", "cdf", "encoded", 256, 16),
+    ("fp8", "cdf", "positions", 64, 8),
 ])
 def test_tile_size_does_not_change_a_ray(precision, select, din, B, N):
     cfg = b.Config(n_bins=B, n_max=N, precision=PREC[precision],
@@ -38,6 +40,10 @@ def test_tile_size_does_not_change_a_ray(precision, select, din, B, N):
     r = b.Renderer(cfg, inputs.make_weights(B, 3, din))
     H, W = 83, 61
     pose = inputs.make_poses([11])
+    tiles = {P: b.donerf_debug_plan(r.cfg, P, H, W, N) for P in (1, 4, 32)}
+    main = {"fp32": 64, "bf16": 256, "fp8": 128}[precision]
+    assert tiles[1]["tile_rays"] != main or tiles[1]["split"] > 1, tiles
+    assert tiles[32]["tile_rays"] == main and tiles[32]["n_full"] > 0, tiles
     alone = {k: v.cpu().numpy() for k, v in r.render(pose, H, W, N, depth=True, debug=True).items()}
     assert np.isfinite(alone["rgb"]).all() and alone["rgb"].max() > 0
     for copies in (4, 32):
@@ -51,18 +57,26 @@ def test_tile_size_does_not_change_a_ray(precision, select, din, B, N):
     r.close()
 
 
-@pytest.mark.parametrize("precision", ["fp32", "bf16", "fp8"])
-def test_single_rays_match_a_frame(precision):
-    """Frames of 1, 31, 33, 63 and 65 rays (one row of the same view: the
-    tiles' edges) against themselves embedded in a batch of 32 views."""
+@pytest.mark.parametrize("precision,tile", [("fp32", 64), ("bf16", 64), ("bf16", 256), ("fp8", 64), ("fp8", 128)])
+def test_single_rays_match_a_frame(precision, tile):
+    """One row of 1, 31, 33, 63 and 65 rays (tiles of 32 and their edges) against
+    the middle row of frames of as many columns and an odd number of rows, which
+    looks through the same pixels, in batches of 32 views that the planner renders
+    on larger tiles and whose last tile is not full."""
     r = b.Renderer(b.Config(precision=PREC[precision], n_max=4), inputs.make_weights(128, 3))
     poses = inputs.make_poses(range(32))
+
+    def plan(P, H, W):
+        return b.donerf_debug_plan(r.cfg, P, H, W, 4)
+
     for W in (1, 31, 33, 63, 65):
-        batch = r.render(poses, 1, W, 4, depth=True, debug=True)
+        H = next(h for h in range(3, 4000, 2) if plan(32, h, W)["tile_rays"] == tile and 32 * h * W % tile)
+        assert plan(1, 1, W)["tile_rays"] == 32
+        batch = r.render(poses, H, W, 4, depth=True, debug=True)
         for i in (0, 31):
             one = r.render(poses[i:i + 1], 1, W, 4, depth=True, debug=True)
             torch.cuda.synchronize()
             for k in ("scores", "bins", "samples"):
-                assert torch.equal(one[k][0], batch[k][i]), (W, i, k)
-            assert float((one["rgb"][0] - batch["rgb"][i]).abs().max()) <= 4e-7
+                assert torch.equal(one[k][0, 0], batch[k][i, H // 2]), (W, i, k)
+            assert float((one["rgb"][0, 0] - batch["rgb"][i, H // 2]).abs().max()) <= 4e-7
     r.close()

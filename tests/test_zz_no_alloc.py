@@ -1,10 +1,10 @@
 """donerf_render_static_scratch, the render for callers that cannot
 allocate: through the C ABI it must give donerf_render's results bit for bit
 (the same kernels; only the split tail's scratch lives in the library's
-static device array), on two calls in a row, the second with a smaller
-input, so the second reuses the array the first left behind.  The shapes
-leave a partial last round of tiles, so the split tail and its scratch are
-used."""
+static device array), on three calls in a row, each with a smaller input, so
+that it reuses the array the ones before left behind.  The largest and the
+smallest leave a partial last round of tiles, so the split tail and its scratch
+are used."""
 import numpy as np
 import pytest
 import torch
@@ -33,9 +33,14 @@ def test_static_scratch_matches_render(precision, N, B, select):
     prec = {"bf16": b.BF16, "fp32": b.FP32, "fp8": b.FP8}[precision]
     sel = b.SELECT_CDF if select == "cdf" else b.SELECT_TOPN
     r = b.Renderer(b.Config(n_bins=B, n_max=N, precision=prec, select=sel), inputs.make_weights(B, 0))
-    # 2 x 96 x 80 rays: 60 (bf16, fp8) or 120 (fp32) tiles, a partial round
-    # split by samples; then 1 x 33 x 29 rays: 4 or 8 tiles, split again
-    for poses, H, W in ((inputs.make_poses([0, 3]), 96, 80), (inputs.make_poses([5]), 33, 29)):
+    # the main kernel's tiles with a split last round; then a part of a round; then
+    # tiles of 32 rays, split again
+    main = {"bf16": 256, "fp32": 64, "fp8": 128}[precision]
+    big, small = (b.donerf_debug_plan(r.cfg, P, H, W, N) for P, H, W in ((3, 150, 151), (1, 33, 29)))
+    assert big["tile_rays"] == main and big["n_full"] > 0 and big["split"] > 1, big
+    assert small["tile_rays"] == 32 and small["split"] > 1, small
+    for poses, H, W in ((inputs.make_poses([1, 2, 4]), 150, 151), (inputs.make_poses([0, 3]), 96, 80),
+                        (inputs.make_poses([5]), 33, 29)):
         ref = _render(r, b.donerf_render, poses, H, W, N)
         got = _render(r, b.donerf_render_static_scratch, poses, H, W, N)
         assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1]), (H, W)
