@@ -22,13 +22,15 @@
 // rays 32 w .. 32 w + 31, lanes l and l + 32 the same ray, as in render_kernel.h.
 //
 // Measured against 32-ray waves on a shared weight stream (256-ray tiles, one
-// workgroup per CU): 5 x 400 x 400, N = 4: 1,344 -> 1,301 us (MFMA pipes busy
-// 59 -> 63 %); 1920 x 1080, N = 2, 192 classes: 2,224 -> 2,189 us; inverse CDF, 2 x
-// 400 x 400, N = 4: 600 -> 584 us; 167 x 167, N = 1: 46 -> 36 us.  With all-zero
-// weights, which leave the clock at 2.4 GHz, 1,212 -> 1,146 us: on real ones the
-// clock is held near 2.0 GHz by the power limit, and the rest of the gain goes
-// into that.  Without the priorities 1.5 % slower, with a third B fragment in
-// flight 1 % (it spills).
+// workgroup per CU), in turn on one box: 5 x 400 x 400, N = 4: 1,379 -> 1,320 us
+// (MFMA pipes busy 59 -> 67 %); 1920 x 1080, N = 2, 192 classes: 2,270 -> 2,217 us;
+// 131,072 rays, N = 16: top-N 768 -> 741 us, inverse CDF 814 -> 734 us (128 classes)
+// and 784 -> 754 us (192).  N = 1 with 192 or 256 classes is level (up to 2 % slower
+// where a last round leaves two tiles on a few CUs).  With all-zero weights, which
+// leave the clock at 2.4 GHz, 1,212 -> 1,073 us against 1,392 us on real ones of the
+// same box: about half of what is left above the MFMAs' own time is the power
+// limit, the rest epilogues that meet no MFMAs of the other workgroup.  Without the
+// priorities 1.5 % slower.
 //
 // The MFMA steps, fragments and K order are rows_kernel.h's, so a ray's scores,
 // classes and samples do not depend on which kernel renders it.

@@ -13,8 +13,8 @@
 // L2 read of a whole layer per R rays: small tiles trade that for using more
 // CUs.  Measured per layer and workgroup, every CU busy: bf16 R = 32 2,400
 // cycles for 128 KiB (53 of the 64 bytes per cycle a CU takes from L2), R = 64
-// 3,250 (2,048 of them MFMAs); fp8 R = 32 1,550 for 64 KiB; fp32 R = 64 16,400
-// (12,288 of them MFMAs).
+// 3,250 (2,048 of them MFMAs); fp8 R = 32 1,550 for 64 KiB.  fp32 R = 64 is bound
+// by its MFMAs (12,288 cycles per layer, 63 % of all) and the epilogues between.
 //
 // bf16 and fp8 networks run the same MFMA steps on the same packed fragments in
 // the same K order as render_kernel.h, so scores, classes and samples are
@@ -28,10 +28,12 @@
 // w1 x1 in one fp32 accumulator, w1 x2 + w2 x1 + w2 x2 + w1 x3 + w3 x1 in a
 // second, added at the end.  Six steps of 1,024 FLOP per cycle and SIMD against
 // 64 for v_mfma_f32_32x32x2_f32: 2.7 times the rate of the fp32 instruction.
-// Against fp32 MFMAs in 128-ray tiles: 400 x 400, N = 4, 4,955 -> 3,070 us
-// (MFMA pipes 57 % busy, 88 % before), 32 x 32 (tiles of 32 rays: 128 CUs, 32
-// before) 412 -> 72 us; image error against 64 bits 2.0e-6 -> 1.1e-6 and
-// 4.6e-7 -> 2.6e-7.
+// Against fp32 MFMAs in 128-ray tiles: 400 x 400, N = 4, 4,927 -> 2,946 us
+// (MFMA pipes 63 % busy, 88 % before), 32 x 32 (tiles of 32 rays: 128 CUs, 32
+// before) 410 -> 66.6 us.  The images' error against 64 bits (2-norm, relative)
+// falls by 1.8: 7.1e-7 -> 4.0e-7 and 3.4e-7 -> 1.8e-7 (two 400 x 400 images), 2.5e-7
+// -> 1.4e-7 (32 x 32); a ray whose N-th and next class are a near-tie may select
+// either, with either arithmetic.
 #pragma once
 
 #include "render_kernel.h"
@@ -53,7 +55,8 @@ DN_HD constexpr int rows_layer_frags(int net, int kind, int n_bins) {
 // sample makes again are loop-invariant, and hoisted out they would be held in
 // registers throughout.  It passes the asm as a pointer to global memory: from a
 // generic one the loads would be flat_load, which take a 64-bit address in VGPRs
-// each, count as LDS accesses too and so make every wait a wait for all.
+// each, count as LDS accesses too and so make every wait a wait for all (fp32, 400 x
+// 400, N = 4: 3,072 -> 2,982 us; 32 x 32: 72.4 -> 66.8; 128 x 128, bf16, 3 % less).
 __device__ __forceinline__ const u32x4* opaque(const u32x4* p) {
     auto q = (const __attribute__((address_space(1))) u32x4*)p;
     asm volatile("" : "+s"(q));
@@ -87,9 +90,8 @@ __device__ __forceinline__ void split3(const float* f, u32x4 (&o)[3]) {
 // sum would be (infinite, or NaN) and lo anything, and a hi that overflows may
 // meet an infinite lo of the other sign: held to finite values (v_med3_f32
 // gives a finite one for NaN), lo leaves such a hi as it is.  The instruction per
-// value costs 1 % (400 x 400, N = 4: 2,969 -> 3,002 us; 32 x 32: 72.2 -> 72.8);
-// looking for such a lo over the wave first (v_maximum3_f32, a branch) costs 0.6 %
-// and 1.9 %.
+// value costs 1 % (400 x 400, N = 4, and 32 x 32 alike); looking for such a lo over
+// the wave first (v_maximum3_f32, a branch) costs 0.6 % and 1.9 %.
 template <class V>
 __device__ __forceinline__ V join(V hi, V lo) {
 #pragma unroll
