@@ -369,11 +369,12 @@ struct TailPlan {
 //   depth + pos + per_b B / 64 + (cdf N / 4, or topn per 4 entries of the list)
 //         + N sample:
 // the depth network with the launch, what the positions input takes longer (its
-// first layer runs on fp32 MFMAs), the head, the placement, the shading network.  A last round on part of the chip takes a share of that: alone if no
-// CU has two tiles, otherwise light + (1 - light) times the share of tiles there
-// (fewer busy CUs clock higher).  Splitting the last round costs combine +
-// combine_part per part.  The first entry of a precision is its main kernel's
-// tile, the others rows_kernel.h's.
+// first layer runs on fp32 MFMAs), the head, the placement, the shading network.
+// A last round on part of the chip takes a share of that: alone if no CU has two
+// tiles, otherwise light + (1 - light) times the share of tiles there (fewer busy
+// CUs clock higher).  Splitting the last round costs combine + combine_part per
+// part.  The first entry of a precision is its main kernel's tile, the others
+// rows_kernel.h's.
 //
 // The fp8 entries are fits over 1,170 random calls (300 to 260,000 rays, N = 1 to
 // 16, every B, both placements and depth inputs), each timed with every tile and
